@@ -14,7 +14,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libgraphattn.so")
-SOURCES = ["api.cpp", "sched.hip", "seg_attn.hip", "merge.hip", "kv_write.hip",
+SOURCES = ["api.cpp", "sched.hip", "seg_attn.hip", "mq_attn.hip", "merge.hip", "kv_write.hip",
            "equiv.hip", "equiv_api.cpp", "reward.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

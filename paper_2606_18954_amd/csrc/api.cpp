@@ -78,7 +78,9 @@ struct Sizes {
   int32_t S0 = 0, B0q = 0, CS = 0;   // segments; branches of a multi-query plan; chain entries
   int64_t P0 = 0;                    // entries of the page table as given
   int32_t chunk_pages = 0;
-  bool few_pages = false;      // under 64 pages (x kv-heads) per workgroup at two per CU
+  bool few_pages = false;      // decode: under 64 pages (x kv-heads) per workgroup at two per CU;
+                               // multi-query: few query rows per page (size_schedule)
+  bool direct = false;         // every query row has one partial: no merge (multi-query plans)
   int64_t max_items = 0;       // upper bound on work items per kv-head
   int32_t desc_words = 0;      // work-item descriptor stride (int32 words)
   int64_t prows = 0;           // partial rows per q-head
@@ -318,11 +320,18 @@ ga_status compress_chains(const ga_segment_table* st, const ga_branch_paths* bp,
 // follow the pages each chain owns (npg_cap >= npg), so that any later lengths fit.
 void size_schedule(const ga_segment_table* st, const ga_branch_paths* bp, const ga_params* p,
                    const std::vector<int32_t>& npg, const std::vector<int64_t>& npg_cap,
-                   int num_cus, Sizes* z) {
-  std::vector<char> used(z->S, 0);
-  for (int64_t e = 0; e < z->E; ++e) used[bp->path_segs[e]] = 1;
-  int64_t ref_pages = 0;
-  for (int32_t s = 0; s < z->S; ++s) ref_pages += used[s] ? npg[s] : 0;
+                   int num_cus, bool causal, bool multi_query, Sizes* z) {
+  const int32_t group = p->num_q_heads / p->num_kv_heads;
+  std::vector<int32_t> used(z->S, 0);             // |B(s)|
+  for (int64_t e = 0; e < z->E; ++e) ++used[bp->path_segs[e]];
+  int64_t ref_pages = 0, block_pages = 0, row_pages = 0;   // pages; x row blocks; x query rows
+  for (int32_t s = 0; s < z->S; ++s) {
+    if (!used[s]) continue;
+    const int64_t rows = (int64_t)used[s] * group;
+    ref_pages += npg[s];
+    block_pages += npg[s] * ((rows + ga::kRowsPerBlock - 1) / ga::kRowsPerBlock);
+    row_pages += npg[s] * rows;
+  }
   // About 4 work items per resident workgroup, in chunks of at most 128 pages (longer units
   // leave too long a tail once the queue is empty; a little fewer at group size 1, so that the
   // descriptor's list of up to 128 branches still fits its slot), and no chunk shorter than the
@@ -332,17 +341,30 @@ void size_schedule(const ga_segment_table* st, const ga_branch_paths* bp, const 
   // chunks also mean fewer partial rows to merge and fewer items to schedule.
   const int64_t wgs = 2LL * num_cus;
   const int64_t target_items = 4 * wgs;
-  const int64_t work = ref_pages * p->num_kv_heads;
+  // Multi-query plans whose pages are read for many rows run mq_attn.hip, whose four waves each own
+  // 32 rows of a block.  Its units are sized by the pages of every row block (each is a unit), and
+  // not cut below 16 pages, so that short prompts keep one partial per row and need no merge.  The
+  // lines lie where the two kernels cross (us per step, other kernel | mq_attn): 16 step trees of
+  // 28/4 heads, 2 queries (35 rows a page) 52 | 62, 4 queries (70 rows, 35 pages a workgroup) 64.7 |
+  // 66.2, 8 queries (140 rows) 87 | 79; one tree of 40/8 heads, 8 queries (100 rows, 4 pages a
+  // workgroup) 38.6 | 42.2, 32 queries 121 | 54; merged DAGs of 24 prompts, 2 queries (56 rows, 200
+  // pages a workgroup) 249 | 245; 12/12 heads x 64, 8 queries (32 rows) 269.6 | 273.6.  One query per
+  // branch stays on the other kernel, whose bits decode has.
+  const bool many_rows =
+      multi_query && p->dtype == GA_BF16 &&
+      (row_pages >= 128 * ref_pages ||
+       (row_pages >= 48 * ref_pages && block_pages * p->num_kv_heads >= 64 * wgs));
+  const int64_t work = (many_rows ? block_pages : ref_pages) * p->num_kv_heads;
   int64_t cap = (work + target_items - 1) / target_items;
   const int32_t max_cap = ga::max_chunk_pages(p->num_q_heads / p->num_kv_heads);
   if (cap > max_cap) cap = max_cap;
-  const int64_t floor_pages = std::min<int64_t>(24, std::max<int64_t>(4, (work + wgs - 1) / wgs));
+  const int64_t floor_pages =
+      std::min<int64_t>(24, std::max<int64_t>(many_rows ? 16 : 4, (work + wgs - 1) / wgs));
   if (cap < floor_pages) cap = floor_pages;
   z->chunk_pages = (int32_t)cap;
   // A step this small gives each workgroup one or two units, whose fixed costs (first pages'
   // latency, partial stores) three workgroups per CU overlap better than two (bf16 decode).
-  z->few_pages = work < 64 * wgs;
-  const int32_t group = p->num_q_heads / p->num_kv_heads;
+  z->few_pages = causal ? !many_rows : work < 64 * wgs;
   int64_t chunks_ref = 0, prows = 0;
   for (int32_t s = 0; s < z->S; ++s)
     if (used[s]) chunks_ref += (npg_cap[s] + cap - 1) / cap;
@@ -634,7 +656,9 @@ ga_status plan_init(const ga_segment_table* st, const ga_branch_paths* bp, const
     pl->z.CS = (int32_t)c.chain_segs.size();
     pl->z.B0q = query_counts ? bp->num_branches : 0;
   }
-  size_schedule(&cst, &cbp, p, c.npg, npg_cap, pl->num_cus, &pl->z);
+  size_schedule(&cst, &cbp, p, c.npg, npg_cap, pl->num_cus,
+                query_counts != nullptr, query_counts && pl->z.B > bp->num_branches, &pl->z);
+  pl->z.direct = query_counts && !pl->z.few_pages && !p->out_f32 && pl->z.prows == pl->z.B;
   if (pl->z.prows > 0x7fffffffLL)
     return fail(GA_EINVAL, "too many partial rows (%lld)", (long long)pl->z.prows);
   if (pl->z.P > 0x7fffffffLL)
@@ -737,6 +761,10 @@ ga_status do_run(ga_plan* pl, const void* q, const void* pool, void* out, float*
   a.desc_words = pl->z.desc_words;
   a.streams = ga::attn_streams(a.Hkv, pl->causal);
   a.scale_log2 = pl->p.softmax_scale * 1.4426950408889634f;
+  if (pl->z.direct) {
+    a.out = out;
+    a.lse = lse;
+  }
   int64_t grid = (int64_t)ga::seg_attn_grid(pl->p.head_dim, bf16, pl->causal, pl->z.few_pages,
                                             pl->num_cus);
   const int64_t work = pl->z.max_items * pl->p.num_kv_heads;
@@ -763,11 +791,11 @@ ga_status do_run(ga_plan* pl, const void* q, const void* pool, void* out, float*
   m.counters = pl->sc.counters;
   m.B = pl->z.B;
   m.Hq = pl->p.num_q_heads;
-  const bool merge_rows = (int64_t)m.B * m.Hq > 0;
-  GA_HIP(ga::launch_merge(m, pl->p.head_dim, bf16 && !pl->p.out_f32, bf16, stream,
-                          rec && merge_rows ? ev[2] : nullptr,
-                          rec && merge_rows ? ev[3] : nullptr),
-         "merge launch");
+  const bool merge_rows = (int64_t)m.B * m.Hq > 0 && !pl->z.direct;
+  if (merge_rows)
+    GA_HIP(ga::launch_merge(m, pl->p.head_dim, bf16 && !pl->p.out_f32, bf16, stream,
+                            rec ? ev[2] : nullptr, rec ? ev[3] : nullptr),
+           "merge launch");
   pl->scheduled = true;
   if (rec) {
     if (!merge_rows) {

@@ -74,7 +74,8 @@ struct DevSchedule {
   int4* items;             // [max_items] (segment, chunk, row block, unused)
   int32_t* desc;           // [max_items * desc_words (+ kDescMaxBytes of padding)] descriptors
   int32_t desc_words;      // descriptor stride in int32 words (a multiple of 4)
-  int64_t* counters;       // [8]: items, partial rows, spare, spare, then kMaxStreams int32
+  int64_t* counters;       // [8]: items, partial rows, finished workgroups of a launch
+                           //     without a merge, spare, then kMaxStreams int32
                            //      work-stream heads (the attention kernel's claim counters)
   int64_t* entry_part;     // [E]   first slot of each path entry in the branch partial lists
   int64_t* bpart_off;      // [B+1] CSR offsets of each branch's partial rows
@@ -111,6 +112,10 @@ struct AttnArgs {
   int32_t desc_words;      // descriptor stride (int32 words)
   int32_t streams;         // work streams: divides Hkv and kMaxStreams
   float scale_log2;        // softmax scale * log2(e)
+  // Multi-query launches whose rows all have one partial: the attention kernel writes them itself,
+  // as bf16 (nullptr: partial rows, folded by the merge).
+  void* out;
+  float* lse;
 };
 
 struct MergeArgs {
@@ -219,7 +224,8 @@ hipError_t launch_set_lengths(const LengthArgs& a, hipStream_t stream);
 hipError_t launch_schedule(const DevGraph& g, const DevSchedule& sc, int32_t group,
                            int32_t chunk_pages, int64_t max_items, bool reuse,
                            hipStream_t stream);
-// few_pages: a decode step with under 64 pages (times kv-heads) per workgroup at two per CU.
+// few_pages: a decode step with under 64 pages (times kv-heads) per workgroup at two per CU, or a
+// multi-query step with few query rows per page (bf16 steps with many run mq_attn.hip).
 // t0 / t1 (optional, timing events): bound to the kernel's own dispatch (hipExtLaunchKernel), so
 // that their elapsed time is the kernel's execution, without the queue's gaps around it.
 hipError_t launch_seg_attn(const AttnArgs& a, int head_dim, bool bf16, bool causal,

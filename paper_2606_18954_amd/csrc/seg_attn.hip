@@ -30,6 +30,7 @@
 // end.  Each work item writes normalised partials o = O / l and lambda = m + log2(l) for every
 // row (fp16 with a per-row power-of-two scale for bf16 inputs, fp32 otherwise); the merge kernel
 // folds them along each branch's path.
+#include "attn_dev.hpp"
 #include "ga_internal.hpp"
 
 #include <hip/hip_ext.h>
@@ -52,13 +53,13 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 // Workgroups per CU and ring depth: two workgroups with four stages for decode; the bf16
-// multi-query variant runs three workgroups per CU (its 128-row units are bound by each wave's
-// issue and compute, so more waves per CU pay more than a deeper ring) with three stages each,
-// and so does bf16 decode on a step with few pages per workgroup (each workgroup then has one
-// or two units, whose fixed costs more workgroups overlap better).  (The fp32 variants keep
+// multi-query variant (steps with few query rows per page; mq_attn.hip takes the others) runs
+// three workgroups per CU with three stages each, and so does bf16 decode on a step with few
+// pages per workgroup (each workgroup then has one or two units, whose fixed costs more
+// workgroups overlap better).  (The fp32 variants keep
 // two: at three their 32 query registers per tile would spill.)
 __host__ __device__ constexpr int attn_wgs_per_cu(bool causal, bool bf16, bool few_pages) {
-  return bf16 && (causal || few_pages) ? 3 : 2;
+  return bf16 && few_pages ? 3 : 2;
 }
 
 template <int D, bool BF16, int WPC = 2>
@@ -79,86 +80,6 @@ struct Cfg {
   static_assert((NBUF - 2) * SP * IPW <= 63, "pending DMA count must fit the wait helper");
 };
 
-// Direct-to-LDS copy of 16 bytes per lane: LDS[lds_base + 16 * lane] <- global[base + off].
-// base (the page block) and lds_base are wave-uniform SGPR values, off a per-lane VGPR.  Issued
-// as inline assembly so that the compiler's wait-count pass does not treat every later LDS read
-// as a possible alias of the copy (it would drain the whole pipeline before each stage);
-// ordering is explicit instead: wait_vmcnt() before the barrier that publishes a stage.  M0
-// holds the LDS base; the kernel keeps no other value in M0.  The copies are non-temporal (nt):
-// every K/V byte is read once per step, and streaming it through the caches at normal priority
-// would evict the partial rows this kernel writes and the merge kernel reads back.
-// The multi-query (causal) variant copies with the normal cache policy instead: there the row
-// blocks of one chunk read the same pages, and the later ones find them in the caches.
-// (tests/test_isa_invariants.py checks in the built assembly that every M0 write is one of these.)
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void dma16(unsigned off, const void* base, unsigned lds_base) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1 nt"
-               :: "v"(off), "s"(base), "s"(lds_base) : "memory", "m0");
-}
-__device__ __forceinline__ void dma16_cached(unsigned off, const void* base, unsigned lds_base) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1"
-               :: "v"(off), "s"(base), "s"(lds_base) : "memory", "m0");
-}
-// Partial-row stores with device scope (sc1): the L2 writes them through to the memory side at
-// once instead of holding them dirty and writing them back later, in the middle of the K/V read
-// stream.  (Same bytes; the merged-DAG attention measured 376 -> 370.5 us.)
-// A store of more than 64 bits reads its data registers one cycle after issue, and the
-// compiler's hazard checks do not look inside inline assembly: the 16-byte store carries its own
-// wait states, or the next instruction may overwrite the data before it is read.
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ void store_dev16(f16x8* p, f16x8 v) {
-  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" :: "v"(p), "v"(v) : "memory");
-}
-__device__ __forceinline__ void store_dev8(f32x2* p, f32x2 v) {
-  asm volatile("global_store_dwordx2 %0, %1, off sc1" :: "v"(p), "v"(v) : "memory");
-}
-#pragma clang diagnostic pop
-
-// s_waitcnt vmcnt(n) for a runtime n in [0, 63] (expcnt and lgkmcnt left alone).  The gfx9
-// encoding splits vmcnt into bits [3:0] and [15:14].
-#define GA_VMCNT(k) (((k) & 15) | (7 << 4) | (15 << 8) | (((k) >> 4) << 14))
-__device__ __forceinline__ void wait_vmcnt(int n) {
-  // Loads placed before the wait in the source must be issued before it: the s_waitcnt builtin
-  // alone does not order ordinary loads, and a load sunk below it would be waited for later,
-  // inside the stage loop, draining the copy ring.
-  asm volatile("" ::: "memory");
-#define GA_VMW(k) case k: __builtin_amdgcn_s_waitcnt(GA_VMCNT(k)); break;
-#define GA_VMW8(b) GA_VMW(b) GA_VMW(b + 1) GA_VMW(b + 2) GA_VMW(b + 3) GA_VMW(b + 4) \
-                   GA_VMW(b + 5) GA_VMW(b + 6) GA_VMW(b + 7)
-  switch (n) {
-    GA_VMW8(0) GA_VMW8(8) GA_VMW8(16) GA_VMW8(24) GA_VMW8(32) GA_VMW8(40) GA_VMW8(48) GA_VMW8(56)
-    default: __builtin_amdgcn_s_waitcnt(GA_VMCNT(0)); break;
-  }
-#undef GA_VMW8
-#undef GA_VMW
-}
-
-template <int N>
-__device__ __forceinline__ void wait_vmcnt_const() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(GA_VMCNT(N));
-}
-
-// Workgroup barrier without a memory fence: LDS-DMA completion is ordered by the explicit
-// vmcnt wait before it; the empty asm statements keep the compiler from moving LDS accesses
-// across it.
-__device__ __forceinline__ void wg_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
-// Barrier for data exchanged through LDS by ordinary LDS writes: waits for this wave's LDS
-// operations only (lgkmcnt(0)), not for its global stores.
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(0xC07F);
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
 // Byte offset of 16-byte chunk `ch` of token `tok` inside a K or V block in LDS.
 template <int D, bool BF16>
 __device__ __forceinline__ int swz(int tok, int ch) {
@@ -174,22 +95,9 @@ __device__ __forceinline__ float xsum(float v) {
   v += __shfl_xor(v, 16);
   return v + __shfl_xor(v, 32);
 }
-__device__ __forceinline__ float exp2_(float x) { return __builtin_amdgcn_exp2f(x); }
-__device__ __forceinline__ float log2_(float x) { return __builtin_amdgcn_logf(x); }
-
 template <bool BF16> struct QOp;
 template <> struct QOp<true> { bf16x8 v; };
 template <> struct QOp<false> { float v; };
-
-__device__ __forceinline__ int64_t uniform64(int64_t v) {
-  const int lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)(uint64_t)v);
-  const int hi = __builtin_amdgcn_readfirstlane((int)((uint64_t)v >> 32));
-  return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
-}
-
-// Scores more than 2^kTau above a row's running reference trigger a reference update; below
-// that the stale reference is kept (probabilities up to 2^kTau are exact in fp32 and bf16).
-constexpr float kTau = 8.0f;
 
 // Online softmax (log2 domain) over NPG pages of 16 tokens for each of the wave's NT tiles
 // (S[g][t]: page g's scores): masks tokens past each page's valid tokens, and moves a row's
@@ -803,7 +711,7 @@ void k_seg_attn(AttnArgs a) {
 template <int D, bool BF16>
 hipError_t launch_t(const AttnArgs& a, bool causal, bool few_pages, int grid,
                     hipStream_t stream, hipEvent_t t0, hipEvent_t t1) {
-  constexpr int W_CAUSAL = attn_wgs_per_cu(true, BF16, false);
+  constexpr int W_CAUSAL = attn_wgs_per_cu(true, BF16, true);
   constexpr int W_WIDE = attn_wgs_per_cu(false, BF16, true);
   constexpr int W_DECODE = attn_wgs_per_cu(false, BF16, false);
   auto go = [&](auto kernel) {
@@ -821,7 +729,7 @@ hipError_t launch_t(const AttnArgs& a, bool causal, bool few_pages, int grid,
 }  // namespace
 
 int seg_attn_grid(int head_dim, bool bf16, bool causal, bool few_pages, int num_cus) {
-  (void)head_dim;
+  if (bf16 && causal && !few_pages) return num_cus * mq_wgs_per_cu(head_dim);
   // 256-thread workgroups (LDS-bound)
   return num_cus * attn_wgs_per_cu(causal, bf16, few_pages);
 }
@@ -829,6 +737,7 @@ int seg_attn_grid(int head_dim, bool bf16, bool causal, bool few_pages, int num_
 hipError_t launch_seg_attn(const AttnArgs& a, int head_dim, bool bf16, bool causal,
                            bool few_pages, int grid, hipStream_t stream, hipEvent_t t0,
                            hipEvent_t t1) {
+  if (bf16 && causal && !few_pages) return launch_mq_attn(a, head_dim, grid, stream, t0, t1);
   if (bf16) {
     if (head_dim == 64) return launch_t<64, true>(a, causal, few_pages, grid, stream, t0, t1);
     if (head_dim == 128) return launch_t<128, true>(a, causal, few_pages, grid, stream, t0, t1);
