@@ -2,6 +2,7 @@
 // the tile list, a cached device workspace, launches, and the two C entry points.
 #include "../../include/graphattn.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -46,7 +47,8 @@ struct Forest {
   std::vector<int2> prompts;     // (first state, states) of the prompts of at most 256 states
   std::vector<int32_t> big;      // the states of the larger prompts
   std::vector<int2> all;         // (first state, states) of every prompt
-  int64_t big_reward = 0;        // states in prompts of more than 512 states
+  int64_t big_reward = 0;        // states in prompts of more than kRewardPromptMax states
+  int32_t max_prompt = 0;        // states of the largest prompt
 };
 
 constexpr int32_t kPromptMax = 256;   // states one workgroup classifies on its own
@@ -113,9 +115,11 @@ ga_status build_forest(const ga_state_forest* f, bool with_items, Forest* fo) {
   fo->big.clear();
   fo->all.clear();
   fo->big_reward = 0;
+  fo->max_prompt = 0;
   for (int32_t r = 0; r < N; r = fo->pend[r]) {
     fo->all.push_back(make_int2(r, fo->pend[r] - r));
-    if (fo->pend[r] - r > 512) fo->big_reward += fo->pend[r] - r;
+    fo->max_prompt = std::max(fo->max_prompt, fo->pend[r] - r);
+    if (fo->pend[r] - r > ga::kRewardPromptMax) fo->big_reward += fo->pend[r] - r;
   }
   if (with_items) {
     for (int32_t r = 0; r < N; r = fo->pend[r]) {
@@ -406,6 +410,7 @@ ga_status graphattn_forest_advantages(ga_forest* forest, const int32_t* labels,
   a.prompts = forest->all;
   a.n_prompts = (int64_t)forest->fo.all.size();
   a.n_big = forest->fo.big_reward;
+  a.max_prompt = forest->fo.max_prompt;
   a.w = w;
   a.lambda_eff = lambda_eff;
   EQ_HIP(ga::launch_advantages(a, static_cast<hipStream_t>(hip_stream)), "advantage launch");

@@ -174,6 +174,10 @@ struct SuffixArgs {
   int64_t N;
 };
 
+// States of a prompt whose rewards one workgroup computes: its arrays (70 bytes a state) then fit
+// the 160 KiB of LDS of a CU.
+constexpr int32_t kRewardPromptMax = 2048;
+
 // Graph reward and dual-group advantage (reward.hip).  Device arrays of N states unless noted.
 struct RewardArgs {
   const int32_t* labels;   // class labels (smallest member)
@@ -192,7 +196,9 @@ struct RewardArgs {
   double *score, *step, *a_cor, *a_eff, *a_dual;   // outputs
   const int2* prompts;     // [n_prompts] (first state, states) of every prompt
   int64_t N, n_prompts;
-  int64_t n_big;           // states in prompts of more than 512 states (0: one launch per batch)
+  int64_t n_big;           // states in prompts of more than kRewardPromptMax states (0: one
+                           // launch per batch)
+  int32_t max_prompt;      // states of the largest prompt
   double w, lambda_eff;
 };
 

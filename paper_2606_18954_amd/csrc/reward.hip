@@ -220,116 +220,154 @@ __global__ void k_dual(RewardArgs a) {
   a.a_dual[v] = c + a.lambda_eff * a.a_eff[v];
 }
 
-// Every prompt of at most kRPromptMax states in one workgroup, its arrays in LDS, one launch:
+// Every prompt of at most kRewardPromptMax states in one workgroup, its arrays in LDS, one launch.
+//
+// What bounds it: latency.  A prompt is a few hundred states, and its phases are chains of LDS
+// round trips between barriers; the 64 bytes a state moves through HBM are nothing beside them.
+// So the phases are few (one block scan for the outcomes and both lists, one for the routes) and
+// their loops short:
 //   outcomes   a prefix sum of the packed (R, 1) values in Euler order (subtrees are ranges);
 //   pooling    class totals by LDS integer atomics;
-//   lists      children and class members as CSR built with LDS atomics and then sorted, so
-//              each state's correctness group reads only its class's children and each class's
-//              efficiency values only its members;
-//   routes     the edge into u sums over u's subtree, read off the Euler order.
+//   lists      children and class members as CSR, a state's place in its list being the number
+//              of smaller ids there, so each state's correctness group reads only its class's
+//              children (and only states with children have a group that is read) and each
+//              class's efficiency values only its members;
+//   routes     the edge into u sums over u's subtree: a range of the Euler order, of which only
+//              the members of classes with an anchor are kept (in that order).
 // The results equal the multi-kernel path's up to the order of a few fp64 sums.
-constexpr int kRPromptMax = 512;
-
-template <typename T>
-__device__ void lds_scan_excl(T* v, int n) {          // exclusive scan of v[0, n] in place
-  __shared__ T tmp[kRPromptMax + 1];
-  for (int i = threadIdx.x; i <= n; i += 256) tmp[i] = v[i];
-  __syncthreads();
-  for (int off = 1; off <= n; off <<= 1) {
-    T add[3] = {0, 0, 0};
-    int k = 0;
-    for (int i = threadIdx.x; i <= n; i += 256, ++k) add[k] = i >= off ? tmp[i - off] : 0;
-    __syncthreads();
-    k = 0;
-    for (int i = threadIdx.x; i <= n; i += 256, ++k) tmp[i] += add[k];
-    __syncthreads();
-  }
-  for (int i = threadIdx.x; i <= n; i += 256) v[i] = i ? tmp[i - 1] : 0;
-  __syncthreads();
+//   512 prompts of 205 states: 49 -> 30 us; 64 prompts of 517 states, which took the multi-kernel
+//   path's scans of the whole prompt per state: 585 -> 23 us.
+// Indices are prompt-local and held in 16 bits; LDS is sized for the batch's largest prompt.
+__host__ __device__ constexpr size_t reward_lds_bytes(int n) {
+  return 8 * (size_t)(5 * n + 1) + 4 * (size_t)(n + 1) + 2 * (size_t)(13 * n + 1);
 }
 
-__device__ void sort_small(int* a, int n) {           // insertion sort of a short list
-  for (int i = 1; i < n; ++i) {
-    const int x = a[i];
-    int j = i - 1;
-    while (j >= 0 && a[j] > x) {
-      a[j + 1] = a[j];
-      --j;
-    }
-    a[j + 1] = x;
-  }
-}
-
-__global__ __launch_bounds__(256) void k_prompt_advantages(RewardArgs a) {
-  __shared__ int s_par[kRPromptMax], s_lab[kRPromptMax], s_dep[kRPromptMax];
-  __shared__ int s_tin[kRPromptMax], s_tout[kRPromptMax], s_eul[kRPromptMax];
-  __shared__ int s_anc[kRPromptMax];
-  __shared__ int s_coff[kRPromptMax + 1], s_kids[kRPromptMax], s_cfill[kRPromptMax];
-  __shared__ int s_moff[kRPromptMax + 1], s_mem[kRPromptMax], s_mfill[kRPromptMax];
-  __shared__ long long s_pre[kRPromptMax + 1];
-  __shared__ unsigned long long s_ctot[kRPromptMax];
-  __shared__ double s_S[kRPromptMax], s_r[kRPromptMax], s_aen[kRPromptMax];
-  __shared__ double s_gm[kRPromptMax], s_gs[kRPromptMax];
+template <int NT>
+__global__ __launch_bounds__(NT) void k_prompt_advantages(RewardArgs a, int cap) {
+  typedef unsigned short u16;
+  constexpr u16 kNone = 0xffff;
+  extern __shared__ __align__(16) unsigned char dyn[];
+  __shared__ long long s_wsum[NT / 64];
+  __shared__ unsigned s_wcnt[NT / 64];
+  // (gs takes pre's place, gm ctot's and cval S's once those have been read)
+  long long* s_pre = reinterpret_cast<long long*>(dyn);            // [cap + 1]
+  double* s_gs = reinterpret_cast<double*>(s_pre);
+  unsigned long long* s_ctot = reinterpret_cast<unsigned long long*>(s_pre + cap + 1);
+  double* s_gm = reinterpret_cast<double*>(s_ctot);
+  double* s_S = reinterpret_cast<double*>(s_ctot + cap);
+  double* s_cval = s_S;
+  double* s_r = s_S + cap;
+  double* s_aen = s_r + cap;
+  unsigned* s_off = reinterpret_cast<unsigned*>(s_aen + cap);      // [cap + 1] children | members
+  u16* s_par = reinterpret_cast<u16*>(s_off + cap + 1);
+  u16* s_lab = s_par + cap;
+  u16* s_dep = s_lab + cap;
+  u16* s_tin = s_dep + cap;
+  u16* s_tout = s_tin + cap;
+  u16* s_eul = s_tout + cap;
+  u16* s_anc = s_eul + cap;
+  u16* s_kids = s_anc + cap;
+  u16* s_mem = s_kids + cap;
+  u16* s_ku = s_mem + cap;                                         // lists in arrival order
+  u16* s_mu = s_ku + cap;
+  u16* s_cdep = s_mu + cap;
+  u16* s_cpos = s_cdep + cap;                                      // [cap + 1]
   const int2 pr = a.prompts[blockIdx.x];
-  const int s0 = pr.x, n = pr.y, tid = threadIdx.x;
+  const int s0 = pr.x, n = pr.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int t0 = a.tin[s0];
-  for (int v = tid; v <= n; v += 256) {
-    s_coff[v] = 0;
-    s_moff[v] = 0;
-    s_pre[v] = 0;
-  }
-  for (int v = tid; v < n; v += 256) {
-    s_ctot[v] = 0;
-    s_cfill[v] = 0;
-    s_mfill[v] = 0;
+  for (int v = tid; v <= n; v += NT) {
+    s_off[v] = 0;
+    if (v < n) s_ctot[v] = 0;
   }
   __syncthreads();
-  for (int v = tid; v < n; v += 256) {               // prompt-local indices throughout
+  // A state's slot in its lists, in order of arrival, waits in s_kids / s_mem until they are built.
+  for (int v = tid; v < n; v += NT) {
     const int g = s0 + v;
     const int l = a.labels[g];
     const int lab = ((l >= s0 && l <= g) ? l : g) - s0;
-    s_lab[v] = lab;
     const int p = a.parent[g];
-    s_par[v] = p >= 0 ? p - s0 : -1;
-    s_dep[v] = a.depth[g];
     const int tin = a.tin[g] - t0;
-    s_tin[v] = tin;
-    s_tout[v] = a.tout[g] - t0;
-    s_eul[tin] = v;
     const int r = a.reward[g];
+    s_lab[v] = (u16)lab;
+    s_par[v] = p >= 0 ? (u16)(p - s0) : kNone;
+    s_dep[v] = (u16)a.depth[g];
+    s_tin[v] = (u16)tin;
+    s_tout[v] = (u16)(a.tout[g] - t0);
+    s_eul[tin] = (u16)v;
     s_pre[tin] = r >= 0 ? (((long long)r << 32) | 1) : 0;
-    if (p >= 0) atomicAdd(&s_coff[p - s0], 1);
-    atomicAdd(&s_moff[lab], 1);
+    if (p >= 0) s_kids[v] = (u16)(atomicAdd(&s_off[p - s0], 1u) & 0xffff);
+    s_mem[v] = (u16)(atomicAdd(&s_off[lab], 0x10000u) >> 16);
   }
   __syncthreads();
   // Exclusive scans over [0, n]: s_pre[k] = sum of the outcome values at Euler positions < k (so
-  // a subtree's sums are s_pre[tout] - s_pre[tin]); s_coff[p] = where p's children start and
-  // s_moff[l] = where the members labelled l start.
-  lds_scan_excl(s_pre, n);
-  lds_scan_excl(s_coff, n);
-  lds_scan_excl(s_moff, n);
-  for (int v = tid; v < n; v += 256) {
-    const int p = s_par[v];
-    if (p >= 0) s_kids[s_coff[p] + atomicAdd(&s_cfill[p], 1)] = v;
-    const int l = s_lab[v];
-    s_mem[s_moff[l] + atomicAdd(&s_mfill[l], 1)] = v;
+  // a subtree's sums are s_pre[tout] - s_pre[tin]); s_off[v] = where v's children start (low half)
+  // and where the members labelled v start (high half).
+  {
+    long long csum = 0;
+    unsigned ccnt = 0;
+    for (int b0 = 0; b0 <= n; b0 += NT) {
+      const int i = b0 + tid;
+      const long long x0 = i < n ? s_pre[i] : 0;
+      const unsigned y0 = i < n ? s_off[i] : 0;
+      long long x = x0;
+      unsigned y = y0;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const long long xu = __shfl_up(x, o);
+        const unsigned yu = __shfl_up(y, o);
+        if (lane >= o) {
+          x += xu;
+          y += yu;
+        }
+      }
+      if (lane == 63) {
+        s_wsum[wave] = x;
+        s_wcnt[wave] = y;
+      }
+      __syncthreads();
+      long long xb = csum;
+      unsigned yb = ccnt;
+      for (int w = 0; w < NT / 64; ++w) {
+        if (w < wave) {
+          xb += s_wsum[w];
+          yb += s_wcnt[w];
+        }
+        csum += s_wsum[w];
+        ccnt += s_wcnt[w];
+      }
+      if (i <= n) {
+        s_pre[i] = xb + x - x0;
+        s_off[i] = yb + y - y0;
+      }
+      __syncthreads();
+    }
+  }
+  auto kid0 = [&](int v) { return (int)(s_off[v] & 0xffff); };
+  auto kid1 = [&](int v) { return (int)(s_off[v + 1] & 0xffff); };
+  auto mem0 = [&](int v) { return (int)(s_off[v] >> 16); };
+  auto mem1 = [&](int v) { return (int)(s_off[v + 1] >> 16); };
+  for (int v = tid; v < n; v += NT) {                // lists; own outcomes -> class totals
+    const int p = s_par[v], l = s_lab[v];
+    if (p != kNone) s_ku[kid0(p) + s_kids[v]] = (u16)v;
+    s_mu[mem0(l) + s_mem[v]] = (u16)v;
+    atomicAdd(&s_ctot[l], (unsigned long long)(s_pre[s_tout[v]] - s_pre[s_tin[v]]));
+    s_anc[v] = kNone;
   }
   __syncthreads();
-  for (int v = tid; v < n; v += 256) {               // lists in ascending order
-    sort_small(s_kids + s_coff[v], s_cfill[v]);
-    sort_small(s_mem + s_moff[v], s_mfill[v]);
-  }
-  __syncthreads();
-  for (int v = tid; v < n; v += 256) {               // own outcomes -> class totals
+  for (int v = tid; v < n; v += NT) {                // lists in ascending order; pooled scores
+    const int p = s_par[v], l = s_lab[v];
+    if (p != kNone) {
+      const int k0 = kid0(p), k1 = kid1(p);
+      int at = k0;
+      for (int k = k0; k < k1; ++k) at += s_ku[k] < v;
+      s_kids[at] = (u16)v;
+    }
+    const int m0 = mem0(l), m1 = mem1(l);
+    int at = m0;
+    for (int k = m0; k < m1; ++k) at += s_mu[k] < v;
+    s_mem[at] = (u16)v;
     const long long own = s_pre[s_tout[v]] - s_pre[s_tin[v]];
-    atomicAdd(&s_ctot[s_lab[v]], (unsigned long long)own);
-    s_anc[v] = -1;
-    s_aen[v] = 0.0;
-  }
-  __syncthreads();
-  for (int v = tid; v < n; v += 256) {               // pooled scores
-    const long long own = s_pre[s_tout[v]] - s_pre[s_tin[v]];
-    const long long tot = (long long)s_ctot[s_lab[v]];
+    const long long tot = (long long)s_ctot[l];
     const double c = (double)(own >> 32), t = (double)(own & 0xffffffffLL);
     const double C = (double)(tot >> 32), T = (double)(tot & 0xffffffffLL);
     const double num = c + a.w * (C - c), den = t + a.w * (T - t);
@@ -338,16 +376,15 @@ __global__ __launch_bounds__(256) void k_prompt_advantages(RewardArgs a) {
     a.score[s0 + v] = S;
   }
   __syncthreads();
-  for (int v = tid; v < n; v += 256) {               // step rewards; class efficiency values
+  for (int v = tid; v < n; v += NT) {                // step rewards; class efficiency values
     const int p = s_par[v];
     double r = __builtin_nan("");
-    if (p >= 0) r = (s_S[v] - s_S[p]) * (1.0 - fmax(0.0, (double)a.edge_sim[s0 + v]));
+    if (p != kNone) r = (s_S[v] - s_S[p]) * (1.0 - fmax(0.0, (double)a.edge_sim[s0 + v]));
     s_r[v] = r;
     a.step[s0 + v] = r;
-    if (s_lab[v] != v) continue;
-    const int* mem = s_mem + s_moff[v];
-    const int m = s_mfill[v];
-    if (m < 2) continue;
+    const u16* mem = s_mem + mem0(v);
+    const int m = mem1(v) - mem0(v);
+    if (s_lab[v] != v || m < 2) continue;
     int lca = mem[0], sdef = 0;
     double ssum = 0.0;
     for (int k = 0; k < m; ++k) {
@@ -356,7 +393,7 @@ __global__ __launch_bounds__(256) void k_prompt_advantages(RewardArgs a) {
         ssum += s_S[x];
         ++sdef;
       }
-      int y = x, z = lca;
+      int y = x, z = lca;                            // lowest common ancestor by depth walking
       while (s_dep[y] > s_dep[z]) y = s_par[y];
       while (s_dep[z] > s_dep[y]) z = s_par[z];
       while (y != z) {
@@ -366,7 +403,7 @@ __global__ __launch_bounds__(256) void k_prompt_advantages(RewardArgs a) {
       lca = y;
     }
     const int anc = s_lab[lca] == v ? s_par[lca] : lca;
-    if (anc < 0) continue;
+    if (anc == kNone) continue;                      // a class holding its prompt's root
     const double gate = sdef > 0 ? ssum / sdef : 0.0;
     double lsum = 0.0;
     for (int k = 0; k < m; ++k) lsum += -(double)(s_dep[mem[k]] - s_dep[anc]);
@@ -381,61 +418,83 @@ __global__ __launch_bounds__(256) void k_prompt_advantages(RewardArgs a) {
       const int x = mem[k];
       const double l = -(double)(s_dep[x] - s_dep[anc]);
       s_aen[x] = sd > 0.0 ? gate * (l - mean) / sd : 0.0;
-      s_anc[x] = anc;
+      s_anc[x] = (u16)anc;
     }
   }
   __syncthreads();
-  for (int u = tid; u < n; u += 256) {               // correctness groups; efficiency per edge
-    const int lu = s_lab[u], du = s_dep[u];
-    const int* mem = s_mem + s_moff[lu];
-    const int m = s_mfill[lu];
-    int cnt = 0, members = 0;
-    double sum = 0.0;
-    for (int k = 0; k < m; ++k) {
-      const int q = mem[k];
-      const int* kid = s_kids + s_coff[q];
-      for (int j = 0; j < s_cfill[q]; ++j) {
-        const int c = kid[j];
-        if (q != u && s_dep[c] <= du) continue;
-        ++members;
-        if (isnan(s_r[c])) continue;
-        sum += s_r[c];
-        ++cnt;
+  // The Euler order's class members with an anchor, and how many lie before each position.
+  {
+    unsigned carry = 0;
+    for (int b0 = 0; b0 <= n; b0 += NT) {
+      const int i = b0 + tid;
+      const int x = i < n ? s_eul[i] : 0;
+      const bool on = i < n && s_anc[x] != kNone;
+      const unsigned long long bal = __ballot(on);
+      if (lane == 0) s_wcnt[wave] = (unsigned)__popcll(bal);
+      __syncthreads();
+      unsigned at = carry;
+      for (int w = 0; w < NT / 64; ++w) {
+        if (w < wave) at += s_wcnt[w];
+        carry += s_wcnt[w];
       }
+      at += (unsigned)__popcll(bal & ((1ull << lane) - 1));
+      if (i <= n) s_cpos[i] = (u16)at;
+      if (on) {
+        s_cval[at] = s_aen[x];
+        s_cdep[at] = s_dep[s_anc[x]];
+      }
+      __syncthreads();
     }
-    double mean = 0.0, sd = 0.0;
-    if (members > 1 && cnt > 0) {
-      mean = sum / cnt;
-      double q2 = 0.0;
-      for (int k = 0; k < m; ++k) {
-        const int q = mem[k];
-        const int* kid = s_kids + s_coff[q];
-        for (int j = 0; j < s_cfill[q]; ++j) {
-          const int c = kid[j];
-          if ((q != u && s_dep[c] <= du) || isnan(s_r[c])) continue;
-          const double d = s_r[c] - mean;
-          q2 += d * d;
+  }
+  for (int u = tid; u < n; u += NT) {                // correctness groups; efficiency per edge
+    if (kid0(u) < kid1(u)) {
+      const int lu = s_lab[u], du = s_dep[u], m0 = mem0(lu), m1 = mem1(lu);
+      int cnt = 0, members = 0;
+      double sum = 0.0;
+      for (int k = m0; k < m1; ++k) {
+        const int q = s_mem[k], k1 = kid1(q);
+        if (q != u && s_dep[q] < du) continue;       // (its children lie no deeper than u)
+        for (int j = kid0(q); j < k1; ++j) {
+          const double r = s_r[s_kids[j]];
+          ++members;
+          if (isnan(r)) continue;
+          sum += r;
+          ++cnt;
         }
       }
-      sd = sqrt(q2 / cnt);
-      if (!(sd > kSpreadFloor)) sd = 0.0;
-    }
-    s_gm[u] = mean;
-    s_gs[u] = sd;
-    double e = 0.0;
-    if (s_par[u] >= 0)
-      for (int pos = s_tin[u]; pos < s_tout[u]; ++pos) {
-        const int x = s_eul[pos];
-        const int an = s_anc[x];
-        if (an >= 0 && s_dep[an] < du) e += s_aen[x];
+      double mean = 0.0, sd = 0.0;
+      if (members > 1 && cnt > 0) {
+        mean = sum / cnt;
+        double q2 = 0.0;
+        for (int k = m0; k < m1; ++k) {
+          const int q = s_mem[k], k1 = kid1(q);
+          if (q != u && s_dep[q] < du) continue;
+          for (int j = kid0(q); j < k1; ++j) {
+            const double r = s_r[s_kids[j]];
+            if (isnan(r)) continue;
+            const double d = r - mean;
+            q2 += d * d;
+          }
+        }
+        sd = sqrt(q2 / cnt);
+        if (!(sd > kSpreadFloor)) sd = 0.0;
       }
+      s_gm[u] = mean;
+      s_gs[u] = sd;
+    }
+    double e = 0.0;
+    if (s_par[u] != kNone) {
+      const int du = s_dep[u], c1 = s_cpos[s_tout[u]];
+      for (int k = s_cpos[s_tin[u]]; k < c1; ++k)
+        if (s_cdep[k] < du) e += s_cval[k];
+    }
     a.a_eff[s0 + u] = e;
   }
   __syncthreads();
-  for (int v = tid; v < n; v += 256) {
+  for (int v = tid; v < n; v += NT) {
     const int p = s_par[v];
     double c = 0.0;
-    if (p >= 0 && !isnan(s_r[v]) && s_gs[p] > 0.0) c = (s_r[v] - s_gm[p]) / s_gs[p];
+    if (p != kNone && !isnan(s_r[v]) && s_gs[p] > 0.0) c = (s_r[v] - s_gm[p]) / s_gs[p];
     a.a_cor[s0 + v] = c;
     a.a_dual[s0 + v] = c + a.lambda_eff * a.a_eff[s0 + v];   // written by this thread above
   }
@@ -446,7 +505,17 @@ __global__ __launch_bounds__(256) void k_prompt_advantages(RewardArgs a) {
 hipError_t launch_advantages(const RewardArgs& a, hipStream_t stream) {
   if (a.N == 0) return hipSuccess;
   if (a.n_big == 0) {
-    hipLaunchKernelGGL(k_prompt_advantages, dim3((unsigned)a.n_prompts), dim3(256), 0, stream, a);
+    // About a thread per state: a prompt's loops then run once, and a batch of many small prompts
+    // keeps several workgroups on a CU.
+    const int cap = (a.max_prompt + 3) & ~3;
+    const size_t lds = reward_lds_bytes(cap);
+    const dim3 grid((unsigned)a.n_prompts);
+    if (cap <= 256)
+      hipLaunchKernelGGL(k_prompt_advantages<256>, grid, dim3(256), lds, stream, a, cap);
+    else if (cap <= 512)
+      hipLaunchKernelGGL(k_prompt_advantages<512>, grid, dim3(512), lds, stream, a, cap);
+    else
+      hipLaunchKernelGGL(k_prompt_advantages<1024>, grid, dim3(1024), lds, stream, a, cap);
     return hipGetLastError();
   }
   const unsigned g = (unsigned)((a.N + kB - 1) / kB);

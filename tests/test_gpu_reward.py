@@ -150,3 +150,44 @@ def test_one_launch_and_multi_kernel_paths_agree():
     multi = gpu_adv(both, labels, reward, sim, 0.7, 0.5)
     for k in KEYS.values():
         assert np.allclose(one[k][:n], multi[k][:n], rtol=0, atol=1e-12, equal_nan=True), k
+
+
+def random_tree(rng, n, kind):
+    if kind == "chain":
+        return np.arange(-1, n - 1, dtype=np.int32)
+    parent = np.zeros(n, dtype=np.int32) if kind == "star" else np.array(
+        [0] + [int(rng.integers(max(0, v - 40), v)) for v in range(1, n)], dtype=np.int32)
+    parent[0] = -1
+    return parent
+
+
+@pytest.mark.parametrize("kind", ["random", "star", "chain"])
+@pytest.mark.parametrize("n", [1, 2, 64, 65, 255, 256, 257, 512, 513, 1024, 1025, 2047, 2048])
+def test_one_launch_sizes(n, kind):
+    """One prompt at the edges of the workgroup sizes and of the one-launch range, alone and next
+    to a prompt beyond that range (2,203 states), which sends both through the multi-kernel path:
+    the two agree to the rounding of the few fp64 sums taken in another order (n terms of size at
+    most sqrt(n) each).  Small prompts also against the oracle."""
+    rng = np.random.default_rng(n)
+    small = random_tree(rng, n, kind)
+    big = W.state_forest(1, (6, 6, 60)) + n
+    big[0] = -1
+    both = np.concatenate([small, big])
+    N = len(both)
+    d = O.state_depths(both)
+    labels = np.arange(N, dtype=np.int32)
+    last = {}
+    for v in range(1, n):                             # classes of states of one depth, some large
+        key = (int(d[v]), int(rng.integers(0, 4)))
+        if rng.random() < 0.5:
+            labels[v] = last.setdefault(key, v)
+    reward = W.state_rewards(both, n)
+    sim = rng.uniform(-0.5, 1.0, N).astype(np.float32)
+    say(f"[case] n={n} {kind} classes={len(set(labels[:n].tolist()))}")
+    one = gpu_adv(small, labels[:n], reward[:n], sim[:n], 0.7, 0.5)
+    multi = gpu_adv(both, labels, reward, sim, 0.7, 0.5)
+    for k in KEYS.values():
+        assert np.allclose(one[k], multi[k][:n], rtol=1e-12, atol=1e-10, equal_nan=True), k
+    if n <= 257 and kind != "chain":
+        compare(f"n={n} {kind}", one, O.graph_advantages(
+            small, labels[:n], reward[:n], sim[:n].astype(np.float64), 0.7, 0.5), tol=1e-9)
