@@ -157,7 +157,9 @@ struct ga_forest {
   int32_t* big = nullptr;
   float* inv_norm = nullptr;
   int* rep = nullptr;
-  int64_t *cnt = nullptr, *off = nullptr, *blk = nullptr;
+  int32_t* cnt = nullptr;
+  int64_t* blk = nullptr;
+  int64_t* total = nullptr;            // (pinned host memory)
   // graph reward scratch
   int32_t *lab = nullptr, *anchor = nullptr;
   int64_t *euler = nullptr, *pre = nullptr, *own = nullptr, *ctot = nullptr;
@@ -194,9 +196,9 @@ ga_status forest_create(const ga_state_forest* forest, hipStream_t stream, ga_fo
   const size_t up = 6 * n4 + align256(sizeof(int4) * fo.items.size()) +
                     align256(sizeof(int2) * fo.prompts.size()) + align256(4 * fo.big.size()) +
                     align256(sizeof(int2) * fo.all.size());
-  const size_t nblk = (size_t)((fo.N + 1023) / 1024);
+  const size_t nblk = (size_t)((fo.N + 255) / 256);
   const size_t scan = align256(8 * (fo.N + 1));
-  const size_t total = up + 2 * n4 + n8 + scan + align256(8 * (nblk + 1))   // classes, suffix
+  const size_t total = up + 3 * n4 + align256(8 * (nblk + 1))               // classes, suffix
                        + 2 * n4 + 3 * n8 + scan + 3 * n8;                     // graph reward
   if (hipMalloc(&f->dev, total) != hipSuccess) {
     (void)hipGetLastError();
@@ -204,13 +206,14 @@ ga_status forest_create(const ga_state_forest* forest, hipStream_t stream, ga_fo
     forest_free(f);
     return efail(GA_ENOMEM, "device workspace of %zu bytes", total);
   }
-  if (hipHostMalloc(&f->pin, up > 0 ? up : 1) != hipSuccess) {
+  if (hipHostMalloc(&f->pin, up + sizeof(int64_t)) != hipSuccess) {
     (void)hipGetLastError();
     f->pin = nullptr;
     forest_free(f);
     return efail(GA_ENOMEM, "pinned staging of %zu bytes", up);
   }
   char* pin = static_cast<char*>(f->pin);
+  f->total = reinterpret_cast<int64_t*>(pin + up);
   size_t o = 0;
   put(pin, o, fo.tin);
   put(pin, o, fo.tout);
@@ -237,10 +240,9 @@ ga_status forest_create(const ga_state_forest* forest, hipStream_t stream, ga_fo
                                    align256(4 * fo.big.size()));
   f->inv_norm = reinterpret_cast<float*>(d + up);
   f->rep = reinterpret_cast<int*>(d + up + n4);
-  f->cnt = reinterpret_cast<int64_t*>(d + up + 2 * n4);
-  f->off = reinterpret_cast<int64_t*>(d + up + 2 * n4 + n8);
-  f->blk = reinterpret_cast<int64_t*>(d + up + 2 * n4 + n8 + scan);
-  char* r = d + up + 2 * n4 + n8 + scan + align256(8 * (nblk + 1));
+  f->cnt = reinterpret_cast<int32_t*>(d + up + 2 * n4);
+  f->blk = reinterpret_cast<int64_t*>(d + up + 3 * n4);
+  char* r = d + up + 3 * n4 + align256(8 * (nblk + 1));
   f->lab = reinterpret_cast<int32_t*>(r);
   f->anchor = reinterpret_cast<int32_t*>(r + n4);
   f->euler = reinterpret_cast<int64_t*>(r + 2 * n4);
@@ -315,28 +317,22 @@ ga_status forest_suffix(ga_forest* f, const int32_t* labels, int64_t* suffix_off
   a.pstart = f->pstart;
   a.pend = f->pend;
   a.cnt = f->cnt;
-  a.off = f->off;
   a.blk = f->blk;
+  a.off = suffix_offsets;
   a.states = suffix_states;
+  a.total = f->total;
+  a.capacity = capacity;
   a.N = N;
-  int64_t n = 0;
-  if (N > 0) {
-    EQ_HIP(ga::launch_suffix_count(a, stream), "suffix count launch");
-    EQ_HIP(hipMemcpyAsync(&n, a.off + N, sizeof n, hipMemcpyDeviceToHost, stream), "total");
-  }
+  *f->total = 0;
+  if (N > 0) EQ_HIP(ga::launch_suffix(a, stream), "suffix launch");
   EQ_HIP(hipStreamSynchronize(stream), "synchronise");
+  const int64_t n = *static_cast<volatile int64_t*>(f->total);
   *total = n;
   if (n > capacity)
     return efail(GA_ERANGE, "graph suffix needs %lld entries, capacity is %lld", (long long)n,
                  (long long)capacity);
   if (n > 0 && !suffix_states) return efail(GA_EINVAL, "suffix_states is NULL");
-  if (N == 0) {
-    EQ_HIP(hipMemsetAsync(suffix_offsets, 0, sizeof(int64_t), stream), "offsets");
-    return GA_OK;
-  }
-  EQ_HIP(hipMemcpyAsync(suffix_offsets, a.off, sizeof(int64_t) * (N + 1),
-                        hipMemcpyDeviceToDevice, stream), "offsets");
-  EQ_HIP(ga::launch_suffix_fill(a, stream), "suffix fill launch");
+  if (N == 0) EQ_HIP(hipMemsetAsync(suffix_offsets, 0, sizeof(int64_t), stream), "offsets");
   return GA_OK;
 }
 

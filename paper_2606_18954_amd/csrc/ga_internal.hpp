@@ -167,11 +167,14 @@ struct SuffixArgs {
   const int32_t* depth;    // [N]
   const int32_t* pstart;   // [N]  first state of the state's prompt
   const int32_t* pend;     // [N]  one past its last state
-  int64_t* cnt;            // [N]  |C_g(u)|
-  int64_t* off;            // [N + 1] CSR offsets
-  int64_t* blk;            // [ceil(N / 1024)] scan block totals
-  int32_t* states;         // [total] output
+  int32_t* cnt;            // [N]  |C_g(u)|
+  int64_t* blk;            // [ceil(N / 256) + 1] totals of 256 states each
+  int64_t* off;            // [N + 1] output: CSR offsets
+  int32_t* states;         // [capacity] output
+  int64_t* total;          // entries of the lists (pinned host memory)
+  int64_t capacity;        // offsets and lists are written only if they fit
   int64_t N;
+  int64_t nblk;            // (set by the launcher)
 };
 
 // States of a prompt whose rewards one workgroup computes: its arrays (70 bytes a state) then fit
@@ -242,8 +245,7 @@ hipError_t launch_merge(const MergeArgs& a, int head_dim, bool out_bf16, bool pa
                         hipStream_t stream, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
 hipError_t launch_kv_write(const KvWriteArgs& a, hipStream_t stream);
 hipError_t launch_equivalence(const EquivArgs& a, hipStream_t stream);
-hipError_t launch_suffix_count(const SuffixArgs& a, hipStream_t stream);
-hipError_t launch_suffix_fill(const SuffixArgs& a, hipStream_t stream);
+hipError_t launch_suffix(SuffixArgs a, hipStream_t stream);
 hipError_t launch_advantages(const RewardArgs& a, hipStream_t stream);
 // Number of co-resident attention workgroups the persistent grid uses on this device.
 int seg_attn_grid(int head_dim, bool bf16, bool causal, bool few_pages, int num_cus);

@@ -123,3 +123,58 @@ def test_forest_plan_serves_several_thresholds():
             assert n == len(rs)
             assert np.array_equal(offs.cpu().numpy(), ro)
             assert np.array_equal(st[:n].cpu().numpy(), rs)
+
+
+@pytest.mark.parametrize("sizes", [[1], [255, 1, 300], [1024, 1025, 3], [2203], [256, 256, 1]])
+def test_suffix_spans(sizes):
+    """Prompts below, at and beyond the staged piece of 1,024 states and the block of 256, with
+    many linked states, against the oracle; a buffer one entry short leaves both outputs as they
+    were."""
+    require_gpu()
+    rng = np.random.default_rng(sum(sizes))
+    parent = []
+    for n in sizes:
+        s0 = len(parent)
+        parent += [-1] + [s0 + int(rng.integers(max(0, v - 30), v)) for v in range(1, n)]
+    parent = np.array(parent, dtype=np.int32)
+    N = len(parent)
+    root = np.maximum.accumulate(np.where(parent < 0, np.arange(N), 0))
+    labels = np.arange(N, dtype=np.int32)
+    first = {}
+    for v in range(N):
+        if rng.random() < 0.6:
+            labels[v] = first.setdefault((int(root[v]), int(rng.integers(0, 40))), v)
+    ro, rs = O.graph_suffix(labels, parent)
+    say(f"[case] {sizes}: {len(rs)} entries")
+    with G.Forest(parent) as f:
+        lab = torch.from_numpy(labels).cuda()
+        offs = torch.full((N + 1,), -7, dtype=torch.int64, device="cuda")
+        st = torch.full((len(rs) + 3,), -7, dtype=torch.int32, device="cuda")
+        if len(rs):
+            with pytest.raises(G.GraphAttnError) as e:
+                f.suffix(lab, offs, st[:len(rs) - 1])
+            assert e.value.status == G.GA_ERANGE
+            torch.cuda.synchronize()
+            assert (offs == -7).all() and (st == -7).all()
+        assert f.suffix(lab, offs, st) == len(rs)
+        torch.cuda.synchronize()
+        assert np.array_equal(offs.cpu().numpy(), ro)
+        assert np.array_equal(st[:len(rs)].cpu().numpy(), rs) and (st[len(rs):] == -7).all()
+
+
+def test_suffix_of_many_blocks():
+    """More than 4,096 blocks of 256 states (the block totals are then scanned by a kernel of
+    their own): without classes a state's list is its children."""
+    require_gpu()
+    n = 210_000
+    parent = np.tile(np.array([-1, 0, 0, 1, 1], dtype=np.int32), n)
+    parent = np.where(parent < 0, -1, parent + 5 * np.repeat(np.arange(n, dtype=np.int32), 5))
+    N = len(parent)
+    with G.Forest(parent.astype(np.int32)) as f:
+        lab = torch.arange(N, dtype=torch.int32, device="cuda")
+        offs = torch.empty(N + 1, dtype=torch.int64, device="cuda")
+        st = torch.empty(4 * n, dtype=torch.int32, device="cuda")
+        assert f.suffix(lab, offs, st) == 4 * n
+        cnt = np.bincount(parent[parent >= 0], minlength=N)
+        assert np.array_equal(offs.cpu().numpy(), np.concatenate([[0], np.cumsum(cnt)]))
+        assert np.array_equal(st.cpu().numpy(), np.nonzero(parent >= 0)[0])
