@@ -4,14 +4,13 @@
 // Two states of one prompt's graph that are neither ancestor nor descendant of each other are
 // compared by the cosine of their embeddings; pairs at or above kappa are linked, and the
 // classes Q(v) are the connected components of the links.  The similarity is a dense
-// contraction over the embedding width, so it runs on bf16 MFMA: one workgroup per 64 x 64
-// tile (row states i0.., column states j0.., both of one prompt, i0 <= j0), the width streamed
-// through LDS in 64-wide stages, each wave holding a 32 x 32 quadrant as 2 x 2 MFMA tiles.  The
-// epilogue tests every pair of the quadrant (u < v, same prompt, not ancestor-related by the
-// Euler intervals of the generation tree, z_u.z_v >= kappa |z_u| |z_v|) and links the qualifying
-// ones at once with a lock-free union-find on a global parent array: the larger root is hooked
-// under the smaller with a compare-and-swap, so every class's final root is its smallest state
-// (a deterministic label, whatever order the links land in).
+// contraction over the embedding width, so it runs on bf16 MFMA, the width streamed through an
+// LDS ring in 32-wide stages that are copied straight from HBM; the squared norms are diagonals
+// of the same products.  The epilogue tests every pair (u < v, not ancestor-related by the Euler
+// intervals of the generation tree, z_u.z_v >= kappa |z_u| |z_v|) and links the qualifying ones at
+// once with a lock-free union-find: the larger root is hooked under the smaller with a
+// compare-and-swap, so every class's final root is its smallest state (a deterministic label,
+// whatever order the links land in).
 //
 // Graph suffix: C_g(u) is u's direct successors plus those of the other members of Q(u) that lie
 // deeper than u (shared edges only point deeper, so the graph stays acyclic).  One thread per
@@ -19,14 +18,13 @@
 // lists in ascending state order.
 #include "ga_internal.hpp"
 
+#include <type_traits>
+
 namespace ga {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-constexpr int kTile = 64;       // states per tile side
-constexpr int kKC = 64;         // embedding components per LDS stage (128 bytes per state row)
 
 __device__ __forceinline__ int load_rep(const int* rep, int x) {
   return __hip_atomic_load(rep + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -57,115 +55,20 @@ __device__ void unite(int* rep, int a, int b) {
   }
 }
 
-// Prompts of more than 256 states: inverse norm of each of their embeddings (NaN for a zero
-// vector, which is then never linked) and the union-find parent reset to a singleton.  One wave
-// per state of the list a.big.
-__global__ __launch_bounds__(256) void k_norms(EquivArgs a) {
-  const int64_t wi = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6;
-  const int lane = threadIdx.x & 63;
-  if (wi >= a.n_big) return;
-  const int64_t w = a.big[wi];
-  const bf16x8* row = reinterpret_cast<const bf16x8*>(a.z + w * a.dim);
-  float s = 0.f;
-  for (int c = lane; c < a.dim / 8; c += 64) {
-    const bf16x8 v = row[c];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) s = fmaf((float)v[i], (float)v[i], s);
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-  if (lane == 0) {
-    a.inv_norm[w] = s > 0.f ? 1.f / sqrtf(s) : __builtin_nanf("");
-    a.rep[w] = (int)w;
-  }
-}
-
-__global__ __launch_bounds__(256) void k_sim_union(EquivArgs a) {
-  __shared__ __align__(16) unsigned char sA[kTile * kKC * 2];
-  __shared__ __align__(16) unsigned char sB[kTile * kKC * 2];
-  const int4 it = a.items[blockIdx.x];        // (first row state, first column state, prompt end)
-  const int i0 = it.x, j0 = it.y, pend = it.z;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int r16 = lane & 15, kg = lane >> 4;
-  const int wm = wave >> 1, wn = wave & 1;
-  // Global -> LDS: thread t moves 16-byte chunk t % 8 of state rows t / 8 and t / 8 + 32 of both
-  // tiles; chunks are XOR-permuted by row so the MFMA operand reads are conflict-free.
-  const int lr = tid >> 3, lc = tid & 7;
-  auto gload = [&](int s0, int r, int kc) {
-    const int s = s0 + r;
-    uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (s < pend) v = *reinterpret_cast<const uint4*>(a.z + (int64_t)s * a.dim + kc * kKC + lc * 8);
-    return v;
-  };
-  auto lds_off = [](int row, int chunk) { return row * (kKC * 2) + ((chunk ^ (row & 7)) << 4); };
-  uint4 ra0 = gload(i0, lr, 0), ra1 = gload(i0, lr + 32, 0);
-  uint4 rb0 = gload(j0, lr, 0), rb1 = gload(j0, lr + 32, 0);
-  f32x4 acc[2][2];
-#pragma unroll
-  for (int x = 0; x < 2; ++x)
-#pragma unroll
-    for (int y = 0; y < 2; ++y) acc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int nk = a.dim / kKC;
-  for (int kc = 0; kc < nk; ++kc) {
-    __syncthreads();                            // every wave is done with the previous stage
-    *reinterpret_cast<uint4*>(sA + lds_off(lr, lc)) = ra0;
-    *reinterpret_cast<uint4*>(sA + lds_off(lr + 32, lc)) = ra1;
-    *reinterpret_cast<uint4*>(sB + lds_off(lr, lc)) = rb0;
-    *reinterpret_cast<uint4*>(sB + lds_off(lr + 32, lc)) = rb1;
-    __syncthreads();
-    if (kc + 1 < nk) {                          // next stage's loads overlap this stage's MFMAs
-      ra0 = gload(i0, lr, kc + 1);
-      ra1 = gload(i0, lr + 32, kc + 1);
-      rb0 = gload(j0, lr, kc + 1);
-      rb1 = gload(j0, lr + 32, kc + 1);
-    }
-#pragma unroll
-    for (int ks = 0; ks < kKC / 32; ++ks) {
-      bf16x8 av[2], bv[2];
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        av[t] = *reinterpret_cast<const bf16x8*>(sA + lds_off(wm * 32 + t * 16 + r16, ks * 4 + kg));
-        bv[t] = *reinterpret_cast<const bf16x8*>(sB + lds_off(wn * 32 + t * 16 + r16, ks * 4 + kg));
-      }
-#pragma unroll
-      for (int x = 0; x < 2; ++x)
-#pragma unroll
-        for (int y = 0; y < 2; ++y)
-          acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[x], bv[y], acc[x][y], 0, 0, 0);
-    }
-  }
-  // acc[x][y][i] = z_u . z_v with u the row state (4 kg + i of row tile x), v the column state
-  // (r16 of column tile y).
-#pragma unroll
-  for (int y = 0; y < 2; ++y) {
-    const int v = j0 + wn * 32 + y * 16 + r16;
-    if (v >= pend) continue;
-    const int tin_v = a.tin[v], tout_v = a.tout[v];
-    const float nv = a.inv_norm[v];
-#pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int u = i0 + wm * 32 + x * 16 + 4 * kg + i;
-        if (u >= v) continue;
-        const int tin_u = a.tin[u], tout_u = a.tout[u];
-        const bool related = (tin_u <= tin_v && tin_v < tout_u) || (tin_v <= tin_u && tin_u < tout_v);
-        const float cs = acc[x][y][i] * a.inv_norm[u] * nv;
-        if (!related && cs >= a.kappa) unite(a.rep, u, v);
-        if (a.edge_sim && a.parent[v] == u) a.edge_sim[v] = cs;
-      }
-  }
-}
-
 // One prompt of at most 256 states in one workgroup (8 waves).  The prompt's embeddings stream
 // through an LDS ring of 4 stages of 32 components (256 rows x 64 bytes each), 3 stages in
 // flight, copied straight from HBM into LDS (global_load_lds_dwordx4: each lane moves 16 bytes,
 // one wave instruction fills 1 KiB = 16 rows; 16-byte chunks are XOR-permuted by row pair so the
-// MFMA operand reads are conflict-free).  The upper triangle of the 16 x 16 grid of 16 x 16
-// tiles (136 tiles) is dealt out as strips: wave w owns row strips w and 15 - w, i.e. the 16 - w
-// tiles (w, w..15) and the w + 1 tiles (15 - w, 15 - w..15), 17 per wave.  The squared norms
-// are the diagonals of the diagonal tiles (the same fp32 sums as the dot products).  Links are
-// made with a union-find in LDS and the labels written at the end.
+// MFMA operand reads are conflict-free).
+//
+// What bounds it: HBM (each embedding is read once), as long as LDS keeps up.  The upper triangle
+// of 64 x 64 blocks goes to the waves as whole blocks: waves 0 to 5 the six blocks off the
+// diagonal (16 tiles of 16 x 16 from 8 operand reads per stage), waves 6 and 7 two diagonal blocks
+// each (20 tiles from 8 reads), so a stage costs 64 KiB of LDS reads.  Row strips of single tiles
+// (17 tiles from 19 reads per wave, 152 KiB) were bound by them: 194 -> 182 us
+// for 512 prompts of 205 states and width 4096, and 165 us (5.2 TB/s) with the staggered start.
+// The squared norms are the diagonals of the diagonal tiles (the same fp32 sums as the dot
+// products).  Links are made with a union-find in LDS and the labels written at the end.
 constexpr int kPromptMax = 256;
 constexpr int kPKC = 32;                        // components per stage: one MFMA k-step
 constexpr int kPRow = kPKC * 2;                 // bytes of one state row in a stage
@@ -195,8 +98,10 @@ __device__ __forceinline__ void wait_vm(int n) {
   }
 }
 
+// (This wave's operand reads of the stage before have returned, so its slot may be refilled.)
 __device__ __forceinline__ void ring_barrier() {
   asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xC07F);             // lgkmcnt(0)
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 }
@@ -237,7 +142,7 @@ __device__ void lds_unite(int* r, int a, int b) {
   }
 }
 
-__global__ __launch_bounds__(512, 2) void k_prompt_classes(EquivArgs a) {
+__global__ __launch_bounds__(512, 4) void k_prompt_classes(EquivArgs a) {
   __shared__ __align__(1024) unsigned char ring[kPRing * kPStage];
   __shared__ float s_inv[kPromptMax];
   __shared__ int s_tin[kPromptMax], s_tout[kPromptMax], s_rep[kPromptMax], s_par[kPromptMax];
@@ -269,75 +174,321 @@ __global__ __launch_bounds__(512, 2) void k_prompt_classes(EquivArgs a) {
   }
   const unsigned lds_ring = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)ring;
   const int nst = a.dim / kPKC;
+  // Workgroups start at different components and wrap around: rows of a power-of-two width lie on
+  // one memory channel at a time, and all prompts at the same stage crowd onto few of them (182 us
+  // with one start for all, 165 with 64).
+  const int st0 = (int)((int64_t)((blockIdx.x >> 3) & 63) * nst >> 6);
   auto issue = [&](int st) {
+    const int at = st0 + st < nst ? st0 + st : st0 + st - nst;
 #pragma unroll
     for (int j = 0; j < 2; ++j)
-      dma16(coff[j] + (unsigned)(st * kPRow), pbase,
-            __builtin_amdgcn_readfirstlane(lds_ring + (st % kPRing) * kPStage + (2 * wave + j) * 1024));
+      if (2 * wave + j < nt)                      // (strips without states are not copied)
+        dma16(coff[j] + (unsigned)(at * kPRow), pbase,
+              __builtin_amdgcn_readfirstlane(lds_ring + (st % kPRing) * kPStage +
+                                             (2 * wave + j) * 1024));
   };
-  // Strips of this wave and the 17 tiles (strip, column) it owns.
-  const int sa = wave, sb = 15 - wave;
-  auto tile_strip = [&](int k) { return k < 16 - sa ? sa : sb; };
-  auto tile_col = [&](int k) { return k < 16 - sa ? sa + k : k - 1; };
-  f32x4 acc[17];
-#pragma unroll
-  for (int k = 0; k < 17; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  for (int st = 0; st < kPRing - 1 && st < nst; ++st) issue(st);
-  for (int st = 0; st < nst; ++st) {
-    wait_vm(2 * min(nst - 1 - st, kPRing - 2));   // this wave's copies of stage st have landed
+  const int ncp = max(0, min(2, nt - 2 * wave));  // copies of this wave per stage
+  auto next_stage = [&](int st) {
+    wait_vm(ncp * min(nst - 1 - st, kPRing - 2)); // this wave's copies of stage st have landed
     ring_barrier();                               // ... and every wave's; stage st - 1 is done
     if (st + kPRing - 1 < nst) issue(st + kPRing - 1);
-    const unsigned char* stg = ring + (st % kPRing) * kPStage;
-    const bf16x8 a0 = *reinterpret_cast<const bf16x8*>(stg + poff(sa * 16 + r16, kg));
-    const bf16x8 a1 = *reinterpret_cast<const bf16x8*>(stg + poff(sb * 16 + r16, kg));
-#pragma unroll
-    for (int k = 0; k < 17; ++k) {
-      const int srow = tile_strip(k), col = tile_col(k);
-      if (srow < nt && col < nt) {
-        const bf16x8 b = *reinterpret_cast<const bf16x8*>(stg + poff(col * 16 + r16, kg));
-        acc[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(srow == sa ? a0 : a1, b, acc[k], 0, 0, 0);
-      }
-    }
-  }
-  // Squared norms from the diagonal tiles (strip, strip): row 16 strip + m sits in lane
-  // (r16 = m, kg = m / 4), element m % 4.
-#pragma unroll
-  for (int k = 0; k < 17; ++k) {
-    const int srow = tile_strip(k), col = tile_col(k);
-    if (srow != col || srow >= nt) continue;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (4 * kg + i == r16) {
-        const float q = acc[k][i];
-        s_inv[srow * 16 + r16] = q > 0.f ? 1.f / sqrtf(q) : __builtin_nanf("");
-      }
-  }
-  __syncthreads();
-  // acc[k][i] = z_u . z_v, u = 16 strip + 4 kg + i, v = 16 col + r16 (prompt-local).
-#pragma unroll
-  for (int k = 0; k < 17; ++k) {
-    const int srow = tile_strip(k), col = tile_col(k);
-    if (srow >= nt || col >= nt) continue;
+  };
+  const int fo = poff(r16, kg);                   // this lane's chunk of a 16-row strip
+  auto operand = [&](int st, int strip) {
+    return *reinterpret_cast<const bf16x8*>(ring + (st % kPRing) * kPStage + strip * 16 * kPRow +
+                                            fo);
+  };
+  // t[i] = z_u . z_v, u = 16 strip + 4 kg + i, v = 16 col + r16 (prompt-local): a bit per i whose
+  // cosine reaches kappa.
+  auto test_tile = [&](f32x4 t, int strip, int col) {
+    asm volatile("" ::: "memory");                // (no tile's LDS reads move up into another's)
     const int v = col * 16 + r16;
-    if (v >= n) continue;
-    const int tin_v = s_tin[v], tout_v = s_tout[v];
+    uint64_t hit = 0;
+    if (v >= n) return hit;
     const float nv = s_inv[v];
+    const int pv = a.edge_sim ? s_par[v] : -1;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int u = srow * 16 + 4 * kg + i;
+      const int u = strip * 16 + 4 * kg + i;
       if (u >= v) continue;
-      const int tin_u = s_tin[u], tout_u = s_tout[u];
-      const bool related = (tin_u <= tin_v && tin_v < tout_u) || (tin_v <= tin_u && tin_u < tout_v);
-      const float cs = acc[k][i] * s_inv[u] * nv;
-      if (!related && cs >= a.kappa) lds_unite(s_rep, u, v);
-      if (a.edge_sim && s_par[v] == u) a.edge_sim[s0 + v] = cs;
+      const float cs = t[i] * s_inv[u] * nv;
+      if (cs >= a.kappa) hit |= 1u << i;
+      if (pv == u) a.edge_sim[s0 + v] = cs;
+    }
+    return hit;
+  };
+  auto link = [&](int u, int v) {
+    const int tin_u = s_tin[u], tin_v = s_tin[v];
+    const bool related =
+        (tin_u <= tin_v && tin_v < s_tout[u]) || (tin_v <= tin_u && tin_u < s_tout[v]);
+    if (!related) lds_unite(s_rep, u, v);
+  };
+  for (int st = 0; st < kPRing - 1 && st < nst; ++st) issue(st);
+  // Blocks (bi, bj), bi < bj, of waves 0 .. 5; diagonal blocks bi and 3 - bi of waves 6 and 7.  A
+  // wave whose (first) block has no states only copies; strips without states inside a block are
+  // computed on whatever LDS holds, and their results not looked at.
+  const int bi = wave < 3 ? 0 : wave < 5 ? 1 : wave < 6 ? 2 : wave - 6;
+  const int bj = wave < 3 ? wave + 1 : wave < 5 ? wave - 1 : wave < 6 ? 3 : wave - 6;
+  if (64 * bj >= n) {
+    for (int st = 0; st < nst; ++st) next_stage(st);
+    __syncthreads();                              // (the norms)
+  } else if (wave < 6) {
+    f32x4 acc[4][4];
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+      for (int y = 0; y < 4; ++y) acc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int st = 0; st < nst; ++st) {
+      next_stage(st);
+      bf16x8 av[4], bv[4];
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        av[x] = operand(st, 4 * bi + x);
+        bv[x] = operand(st, 4 * bj + x);
+      }
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+#pragma unroll
+        for (int y = 0; y < 4; ++y)
+          acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[x], bv[y], acc[x][y], 0, 0, 0);
+    }
+    __syncthreads();                              // the norms
+    uint64_t hits = 0;                            // bit 16 x + 4 y + i
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+      for (int y = 0; y < 4; ++y)
+        hits |= test_tile(acc[x][y], 4 * bi + x, 4 * bj + y) << (16 * x + 4 * y);
+    for (; hits; hits &= hits - 1) {
+      const int k = __builtin_ctzll(hits);
+      link(64 * bi + 16 * (k >> 4) + 4 * kg + (k & 3), 64 * bj + 16 * ((k >> 2) & 3) + r16);
+    }
+  } else {                                        // two blocks of the diagonal
+    f32x4 acc[2][10];                             // tiles (x, y), x <= y, in row order
+#pragma unroll
+    for (int d = 0; d < 2; ++d)
+#pragma unroll
+      for (int k = 0; k < 10; ++k) acc[d][k] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int st = 0; st < nst; ++st) {
+      next_stage(st);
+#pragma unroll
+      for (int d = 0; d < 2; ++d) {
+        const int bd = d ? 3 - bi : bi;
+        bf16x8 av[4];
+#pragma unroll
+        for (int x = 0; x < 4; ++x) av[x] = operand(st, 4 * bd + x);
+        int k = 0;
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+#pragma unroll
+          for (int y = x; y < 4; ++y, ++k)
+            acc[d][k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[x], av[y], acc[d][k], 0, 0, 0);
+      }
+    }
+    // Squared norms: row 16 strip + m of a diagonal tile sits in lane (r16 = m, kg = m / 4),
+    // element m % 4.
+#pragma unroll
+    for (int d = 0; d < 2; ++d)
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (4 * kg + i == r16) {
+            const float q = acc[d][x * 4 - x * (x - 1) / 2][i];
+            s_inv[64 * (d ? 3 - bi : bi) + 16 * x + r16] =
+                q > 0.f ? 1.f / sqrtf(q) : __builtin_nanf("");
+          }
+    __syncthreads();
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+      const int bd = d ? 3 - bi : bi;
+      if (64 * bd >= n) continue;
+      uint64_t hits = 0;
+      int t = 0;
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+#pragma unroll
+        for (int y = x; y < 4; ++y, ++t)
+          hits |= test_tile(acc[d][t], 4 * bd + x, 4 * bd + y) << (16 * x + 4 * y);
+      for (; hits; hits &= hits - 1) {
+        const int k = __builtin_ctzll(hits);
+        link(64 * bd + 16 * (k >> 4) + 4 * kg + (k & 3), 64 * bd + 16 * ((k >> 2) & 3) + r16);
+      }
     }
   }
   __syncthreads();
   if (tid < n) {
     a.labels[s0 + tid] = s0 + lds_find(s_rep, tid);
     if (a.edge_sim && s_par[tid] < 0) a.edge_sim[s0 + tid] = 0.f;
+  }
+}
+
+// Prompts of more than 256 states: 128 x 128 tiles of their upper triangles, one workgroup each.
+//
+// What bounds it: the L2 reads and LDS reads of the operands against the matrix cores.  64 x 64
+// tiles (16 flops per operand byte) staged through registers, after a pass of their own over the
+// embeddings for the norms, took 322 + 42 us for 64 prompts of 517 states and width 4096; this
+// kernel takes 165 us (590 TFLOP/s over its whole tiles) and no pass before it.
+// Four waves hold a 64 x 64 quadrant each (16 tiles from 8 operand reads per stage); the stages'
+// ring (3 x 16 KiB, two in flight) lets three workgroups share a CU.  The squared norms of a
+// tile's rows and columns are the diagonals of four more products per wave (two row strips and two
+// column strips each: every wave orders its strips so that those come first), so no pass over the
+// embeddings is needed for them.  A quadrant without states, or below the diagonal, only takes part
+// in the copies and norms.  The host deals the tiles of one prompt to one XCD, whose L2 then
+// serves all but the first read of a row.
+constexpr int kTile = 128;
+constexpr int kTStage = 2 * kTile * kPRow;        // rows, then columns: 16 KiB
+constexpr int kTRing = 3;
+
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+// The same copy from a 64-bit address per lane (rows of any width).
+__device__ __forceinline__ void dma16_at(const void* p, unsigned lds_base) {
+  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off"
+               :: "v"(p), "s"(lds_base) : "memory", "m0");
+}
+#pragma clang diagnostic pop
+
+__global__ void k_rep_init(EquivArgs a) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < a.n_big) a.rep[a.big[i]] = a.big[i];
+}
+
+__global__ __launch_bounds__(256, 3) void k_sim_union(EquivArgs a) {
+  __shared__ __align__(1024) unsigned char ring[kTRing * kTStage];
+  __shared__ float s_inv[2][kTile];
+  const int4 it = a.items[blockIdx.x];            // (first row state, first column state, prompt end)
+  const int i0 = it.x, j0 = it.y, pend = it.z;
+  if (i0 >= pend) return;                         // (pads an XCD's list)
+  const bool diag = i0 == j0;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r16 = lane & 15, kg = lane >> 4;
+  const int wm = wave >> 1, wn = wave & 1;
+  const int nst = a.dim / kPKC;
+  // Copies: each wave fills row strips 2 w and 2 w + 1 and, off the diagonal, the column strips of
+  // those numbers; strips without states are left out, rows past the prompt re-read its last state.
+  const unsigned short* src[4];
+  bool have[4];
+  int ncp = 0;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int first = (j < 2 ? i0 : j0) + 16 * (2 * wave + (j & 1));
+    const int row = min(first + (lane >> 2), pend - 1);
+    const int chunk = (lane & 3) ^ ((lane >> 3) & 3);
+    src[j] = a.z + (int64_t)row * a.dim + chunk * 8;
+    have[j] = first < pend && (j < 2 || !diag);
+    ncp += have[j];
+  }
+  const unsigned lds_ring = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)ring;
+  auto issue = [&](unsigned slot) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (have[j]) {
+        dma16_at(src[j], __builtin_amdgcn_readfirstlane(lds_ring + slot + (j >> 1) * (kTStage / 2) +
+                                                        (2 * wave + (j & 1)) * 1024));
+        src[j] += kPKC;
+      }
+  };
+  // Strip x of the wave's rows and of its columns: the two whose norms it computes come first.
+  auto rstrip = [&](int x) { return 4 * wm + (x ^ (2 * wn)); };
+  auto cstrip = [&](int y) { return 4 * wn + (y ^ (2 * wm)); };
+  const int fo = poff(r16, kg), cbase = diag ? 0 : kTStage / 2;
+  f32x4 acc[4][4], sa[2], sb[2];
+#pragma unroll
+  for (int x = 0; x < 2; ++x) sa[x] = sb[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int x = 0; x < 4; ++x) {
+#pragma unroll
+    for (int y = 0; y < 4; ++y) acc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  auto stages = [&](auto quad) {
+    constexpr int NS = decltype(quad)::value ? 4 : 2;
+    unsigned slot = 0, fill = 2 * kTStage;
+    // The norms' sums are all of one sign and lose most where a chain of products is long (3.9e-7
+    // against 3.1e-7 of the similarities at width 4096), so they are taken over 4 stages at a time.
+    for (int b0 = 0; b0 < nst; b0 += 4) {
+      const int b1 = min(b0 + 4, nst);
+      f32x4 qa[2], qb[2];
+#pragma unroll
+      for (int x = 0; x < 2; ++x) qa[x] = qb[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int st = b0; st < b1; ++st) {
+        wait_vm(st + 1 < nst ? ncp : 0);          // this wave's copies of the stage have landed
+        ring_barrier();                           // ... and every wave's; the stage before is done
+        if (st + 2 < nst) issue(fill);
+        bf16x8 av[NS], bv[NS];
+#pragma unroll
+        for (int x = 0; x < NS; ++x) {
+          av[x] = *reinterpret_cast<const bf16x8*>(ring + slot + rstrip(x) * 1024 + fo);
+          bv[x] = *reinterpret_cast<const bf16x8*>(ring + slot + cbase + cstrip(x) * 1024 + fo);
+        }
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+          qa[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[x], av[x], qa[x], 0, 0, 0);
+          qb[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv[x], bv[x], qb[x], 0, 0, 0);
+        }
+        if constexpr (NS == 4) {
+#pragma unroll
+          for (int x = 0; x < 4; ++x)
+#pragma unroll
+            for (int y = 0; y < 4; ++y)
+              acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[x], bv[y], acc[x][y], 0, 0, 0);
+        }
+        fill = slot;
+        slot = slot + kTStage == kTRing * kTStage ? 0 : slot + kTStage;
+      }
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        sa[x] += qa[x];
+        sb[x] += qb[x];
+      }
+    }
+  };
+  issue(0);
+  if (nst > 1) issue(kTStage);
+  const bool quad = i0 + 64 * wm < pend && j0 + 64 * wn < pend && !(diag && wm > wn);
+  if (quad) stages(std::true_type{});
+  else stages(std::false_type{});
+  // Squared norms: row m of a strip sits in lane (r16 = m, kg = m / 4), element m % 4.
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (4 * kg + i == r16) {
+        const float p = sa[x][i], q = sb[x][i];
+        s_inv[0][16 * rstrip(x) + r16] = p > 0.f ? 1.f / sqrtf(p) : __builtin_nanf("");
+        s_inv[1][16 * cstrip(x) + r16] = q > 0.f ? 1.f / sqrtf(q) : __builtin_nanf("");
+      }
+  __syncthreads();
+  if (!quad) return;
+  // acc[x][y][i] = z_u . z_v with u the row state (4 kg + i of strip x), v the column state (r16 of
+  // strip y): a bit (16 x + 4 y + i) per cosine that reaches kappa, then the links.
+  uint64_t hits = 0;
+#pragma unroll
+  for (int y = 0; y < 4; ++y) {
+    const int v = j0 + 16 * cstrip(y) + r16;
+    if (v >= pend) continue;
+    const float nv = s_inv[1][v - j0];
+    const int pv = a.edge_sim ? a.parent[v] : -1;
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int u = i0 + 16 * rstrip(x) + 4 * kg + i;
+        if (u >= v) continue;
+        const float cs = acc[x][y][i] * s_inv[0][u - i0] * nv;
+        if (cs >= a.kappa) hits |= 1ull << (16 * x + 4 * y + i);
+        if (pv == u) a.edge_sim[v] = cs;
+      }
+  }
+  for (; hits; hits &= hits - 1) {
+    const int k = __builtin_ctzll(hits);
+    const int u = i0 + 16 * rstrip(k >> 4) + 4 * kg + (k & 3);
+    const int v = j0 + 16 * cstrip((k >> 2) & 3) + r16;
+    const int tin_u = a.tin[u], tin_v = a.tin[v];
+    const bool related =
+        (tin_u <= tin_v && tin_v < a.tout[u]) || (tin_v <= tin_u && tin_u < a.tout[v]);
+    if (!related) unite(a.rep, u, v);
   }
 }
 
@@ -495,8 +646,7 @@ hipError_t launch_equivalence(const EquivArgs& a, hipStream_t stream) {
   if (a.n_prompts > 0)
     hipLaunchKernelGGL(k_prompt_classes, dim3((unsigned)a.n_prompts), dim3(512), 0, stream, a);
   if (a.n_big > 0) {
-    hipLaunchKernelGGL(k_norms, dim3((unsigned)((a.n_big * 64 + 255) / 256)), dim3(256), 0, stream,
-                       a);
+    hipLaunchKernelGGL(k_rep_init, dim3((unsigned)((a.n_big + 255) / 256)), dim3(256), 0, stream, a);
     if (a.n_items > 0)
       hipLaunchKernelGGL(k_sim_union, dim3((unsigned)a.n_items), dim3(256), 0, stream, a);
     hipLaunchKernelGGL(k_labels, dim3((unsigned)((a.n_big + 255) / 256)), dim3(256), 0, stream, a);

@@ -43,7 +43,7 @@ size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 struct Forest {
   int64_t N = 0;
   std::vector<int32_t> parent, depth, tin, tout, pstart, pend;
-  std::vector<int4> items;       // 64 x 64 tiles of the prompts of more than 256 states
+  std::vector<int4> items;       // 128 x 128 tiles of the prompts of more than 256 states
   std::vector<int2> prompts;     // (first state, states) of the prompts of at most 256 states
   std::vector<int32_t> big;      // the states of the larger prompts
   std::vector<int2> all;         // (first state, states) of every prompt
@@ -52,6 +52,39 @@ struct Forest {
 };
 
 constexpr int32_t kPromptMax = 256;   // states one workgroup classifies on its own
+
+// The upper-triangle tiles of the prompts [first, end).  Workgroups go to the 8 XCDs in turn, so
+// entry 8 k + x runs on XCD x: with 8 prompts and more, all tiles of a prompt are dealt to one XCD
+// (the one with the least work so far), whose L2 then holds what they share; fewer prompts are
+// spread, or XCDs would idle.  Narrow tiles (at most 64 columns), which take about a third of the
+// time, go last and fill the gaps.  Lists are padded with empty tiles.
+std::vector<int4> tile_list(const std::vector<int2>& prompts) {
+  constexpr int32_t kTile = 128;
+  constexpr int kXcds = 8;
+  const int lists = prompts.size() >= (size_t)kXcds ? kXcds : 1;
+  std::vector<int4> full[kXcds], narrow[kXcds];
+  int64_t load[kXcds] = {0};
+  for (const int2& p : prompts) {
+    const int x = (int)(std::min_element(load, load + lists) - load);
+    for (int32_t i0 = p.x; i0 < p.y; i0 += kTile)
+      for (int32_t j0 = i0; j0 < p.y; j0 += kTile) {
+        const bool wide = p.y - j0 > kTile / 2;
+        (wide ? full : narrow)[x].push_back(make_int4(i0, j0, p.y, 0));
+        load[x] += wide ? 3 : 1;
+      }
+  }
+  size_t longest = 0;
+  for (int x = 0; x < lists; ++x) {
+    full[x].insert(full[x].end(), narrow[x].begin(), narrow[x].end());
+    longest = std::max(longest, full[x].size());
+  }
+  std::vector<int4> out;
+  out.reserve(longest * lists);
+  for (size_t k = 0; k < longest; ++k)
+    for (int x = 0; x < lists; ++x)
+      out.push_back(k < full[x].size() ? full[x][k] : make_int4(0, 0, 0, 0));
+  return out;
+}
 
 // Each prompt's states are consecutive, its root first; p(v) < v.  Depths, prompt ranges and
 // Euler intervals (tin <= tin' < tout exactly when the state is an ancestor of the other).
@@ -122,6 +155,7 @@ ga_status build_forest(const ga_state_forest* f, bool with_items, Forest* fo) {
     if (fo->pend[r] - r > ga::kRewardPromptMax) fo->big_reward += fo->pend[r] - r;
   }
   if (with_items) {
+    std::vector<int2> large;
     for (int32_t r = 0; r < N; r = fo->pend[r]) {
       const int32_t e = fo->pend[r];
       if (e - r <= kPromptMax) {
@@ -129,9 +163,9 @@ ga_status build_forest(const ga_state_forest* f, bool with_items, Forest* fo) {
         continue;
       }
       for (int32_t v = r; v < e; ++v) fo->big.push_back(v);
-      for (int32_t i0 = r; i0 < e; i0 += 64)
-        for (int32_t j0 = i0; j0 < e; j0 += 64) fo->items.push_back(make_int4(i0, j0, e, 0));
+      large.push_back(make_int2(r, e));
     }
+    fo->items = tile_list(large);
   }
   return GA_OK;
 }
@@ -155,7 +189,6 @@ struct ga_forest {
   int2* prompts = nullptr;
   int2* all = nullptr;
   int32_t* big = nullptr;
-  float* inv_norm = nullptr;
   int* rep = nullptr;
   int32_t* cnt = nullptr;
   int64_t* blk = nullptr;
@@ -198,7 +231,7 @@ ga_status forest_create(const ga_state_forest* forest, hipStream_t stream, ga_fo
                     align256(sizeof(int2) * fo.all.size());
   const size_t nblk = (size_t)((fo.N + 255) / 256);
   const size_t scan = align256(8 * (fo.N + 1));
-  const size_t total = up + 3 * n4 + align256(8 * (nblk + 1))               // classes, suffix
+  const size_t total = up + 2 * n4 + align256(8 * (nblk + 1))               // classes, suffix
                        + 2 * n4 + 3 * n8 + scan + 3 * n8;                     // graph reward
   if (hipMalloc(&f->dev, total) != hipSuccess) {
     (void)hipGetLastError();
@@ -238,11 +271,10 @@ ga_status forest_create(const ga_state_forest* forest, hipStream_t stream, ga_fo
   f->big = reinterpret_cast<int32_t*>(d + oi + align256(sizeof(int2) * fo.prompts.size()));
   f->all = reinterpret_cast<int2*>(d + oi + align256(sizeof(int2) * fo.prompts.size()) +
                                    align256(4 * fo.big.size()));
-  f->inv_norm = reinterpret_cast<float*>(d + up);
-  f->rep = reinterpret_cast<int*>(d + up + n4);
-  f->cnt = reinterpret_cast<int32_t*>(d + up + 2 * n4);
-  f->blk = reinterpret_cast<int64_t*>(d + up + 3 * n4);
-  char* r = d + up + 3 * n4 + align256(8 * (nblk + 1));
+  f->rep = reinterpret_cast<int*>(d + up);
+  f->cnt = reinterpret_cast<int32_t*>(d + up + n4);
+  f->blk = reinterpret_cast<int64_t*>(d + up + 2 * n4);
+  char* r = d + up + 2 * n4 + align256(8 * (nblk + 1));
   f->lab = reinterpret_cast<int32_t*>(r);
   f->anchor = reinterpret_cast<int32_t*>(r + n4);
   f->euler = reinterpret_cast<int64_t*>(r + 2 * n4);
@@ -286,7 +318,6 @@ ga_status forest_classes(ga_forest* f, const void* embeddings, int32_t dim, int3
   a.big = f->big;
   a.n_prompts = (int64_t)f->fo.prompts.size();
   a.n_big = (int64_t)f->fo.big.size();
-  a.inv_norm = f->inv_norm;
   a.rep = f->rep;
   a.labels = labels;
   a.N = f->fo.N;

@@ -143,10 +143,9 @@ struct KvWriteArgs {
 };
 
 // Equivalence detection (equiv.hip).  z [N][dim] bf16 bits; items: (first row state, first
-// column state, end of their prompt's states, unused) per 64 x 64 tile, row tile <= column tile.
+// column state, end of their prompt's states, unused) per 128 x 128 tile, row tile <= column tile.
 struct EquivArgs {
   const unsigned short* z;
-  float* inv_norm;         // [N]
   int* rep;                // [N]  union-find parents
   const int32_t* tin;      // [N]  Euler interval of each state in its generation tree
   const int32_t* tout;     // [N]

@@ -178,3 +178,48 @@ def test_suffix_of_many_blocks():
         cnt = np.bincount(parent[parent >= 0], minlength=N)
         assert np.array_equal(offs.cpu().numpy(), np.concatenate([[0], np.cumsum(cnt)]))
         assert np.array_equal(st.cpu().numpy(), np.nonzero(parent >= 0)[0])
+
+
+def ragged_forest(sizes, seed):
+    rng = np.random.default_rng(seed)
+    parent = []
+    for n in sizes:
+        s0 = len(parent)
+        parent += [-1] + [s0 + int(rng.integers(max(0, v - 30), v)) for v in range(1, n)]
+    return np.array(parent, dtype=np.int32)
+
+
+SIZES = [([1, 2, 15, 16, 17, 33], 64), ([63, 64, 65], 128), ([127, 128, 129], 64),
+         ([191, 192, 193, 205], 192), ([255, 256], 64), ([257, 130], 64), ([320, 321], 128),
+         ([383, 385], 64), ([517], 192), ([641], 64), ([257, 300, 5] * 5, 64)]
+
+
+@pytest.mark.parametrize("sizes,dim", SIZES)
+def test_classes_and_similarities_at_tile_edges(sizes, dim):
+    """Prompts at the edges of the 16-state strips, of the 64-state blocks of one workgroup and of
+    the 128-state tiles (whole tiles, narrow ones, empty quadrants), and enough of the larger ones
+    that their tiles are dealt to the XCDs.  Labels are exact; edge similarities are two fp32 sums
+    of `dim` products and a reciprocal root each: within (dim + 8) 2^-24 of the float64 cosine,
+    times two for the two norms."""
+    require_gpu()
+    parent = ragged_forest(sizes, sum(sizes))
+    N = len(parent)
+    z = W.draw_state_embeddings(parent, dim, sum(sizes), share=2.0)
+    zb = z.view(torch.int16).numpy().view(np.uint16)
+    kappa = 0.75
+    assert O.similarity_margin(zb, "bf16", parent, kappa) >= MARGIN
+    ref = O.equivalence_classes(zb, "bf16", parent, kappa)
+    zd = z.double().numpy()
+    zd /= np.linalg.norm(zd, axis=1, keepdims=True)
+    sim = np.where(parent < 0, 0.0, (zd * zd[np.maximum(parent, 0)]).sum(1))
+    say(f"[case] {sizes} x {dim}: {len(set(ref.tolist()))} classes")
+    with G.Forest(parent) as f:
+        es = torch.full((N,), -7.0, dtype=torch.float32, device="cuda")
+        for _ in range(2):                            # (the second call finds the first's scratch)
+            lab = f.classes(z.cuda(), kappa, edge_sim=es)
+            torch.cuda.synchronize()
+            assert np.array_equal(lab.cpu().numpy(), ref)
+        err = float(np.abs(es.cpu().numpy().astype(np.float64) - sim).max())
+        say(f"[equiv] similarity max|d| = {err:.1e}")
+        assert err <= 2 * (dim + 8) * 2.0 ** -24
+        assert np.array_equal(f.classes(z.cuda(), kappa).cpu().numpy(), ref)
