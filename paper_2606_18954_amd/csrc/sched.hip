@@ -410,34 +410,91 @@ __device__ __forceinline__ void emit_items(const DevGraph& g, const DevSchedule&
   }
 }
 
+// Partial rows of branch b's path entry with rank r in a group of cnt (nch chunks; first slot in
+// the branch's list, first partial row and first item of the segment given), and b's place in the
+// branch list of every descriptor whose row block holds b's rows.
+__device__ __forceinline__ void emit_entry(const DevSchedule& sc, int group, int chunk_pages, int b,
+                                           int r, int cnt, int nch, int slot, int prow, int w0) {
+  for (int c = 0; c < nch; ++c) sc.bpart[slot + c] = prow + r + c * cnt;
+  const int nrb = (cnt * group + kRowsPerBlock - 1) / kRowsPerBlock;
+  const int rb_lo = (r * group) / kRowsPerBlock;
+  const int rb_hi = (r * group + group - 1) / kRowsPerBlock;
+  for (int c = 0; c < nch; ++c)
+    for (int rb = rb_lo; rb <= rb_hi; ++rb) {
+      const int64_t w = w0 + c * nrb + rb;
+      const int j0 = (rb * kRowsPerBlock) / group;
+      sc.desc[w * sc.desc_words + kDescHead + chunk_pages + (r - j0)] = b;
+    }
+}
+
+// Work item w (segment s, chunk c, row block rb), by one wave: the head of its descriptor and the
+// chunk's page ids.
+__device__ __forceinline__ void emit_item(const DevGraph& g, const DevSchedule& sc, int64_t w, int s,
+                                          int c, int rb, int npg, int nch, int cnt, int goff,
+                                          int prow, int page_off, int lane) {
+  const int p0 = chunk_first_page(c, npg, nch);
+  const int np = chunk_first_page(c + 1, npg, nch) - p0;
+  const int poff = page_off + p0;
+  int32_t* d = sc.desc + w * sc.desc_words;
+  if (lane == 0) {
+    reinterpret_cast<int4*>(d)[0] =
+        make_int4(np, causal_word(g, s, p0), g.seg_len[s] - (npg - 1) * kPageTokens, cnt);
+    reinterpret_cast<int4*>(d)[1] = make_int4(rb, goff, poff, prow + c * cnt);
+  }
+  for (int i = lane; i < np; i += 64) d[kDescHead + i] = g.seg_pages[poff + i];
+}
+
 // The whole scheduler in one workgroup for graphs that fit in LDS (<= kSmallSegs segments,
 // <= kSmallEntries path entries, < kSmallBranches branches): the graph is read once into LDS and
 // every phase works there between workgroup barriers; only outputs go to global memory.  Thread t
 // owns a contiguous run of at most four segments (for the per-segment scans, in segment order and
 // in work-list order) and a contiguous run of at most four branches (for the per-entry work).
+//
+// WIDE: many workgroups each do all of that for themselves (the phases up to the item offsets give
+// every one of them the same values; only the arrival order inside a group differs, which no
+// result depends on), and then write their share of the entries' and items' outputs from LDS;
+// workgroup 0 writes the per-segment ones.  The alternative, one workgroup whose results k_emit
+// reads back from memory, pays a launch, and every entry and item of k_emit two to three dependent
+// loads.  What bounds both is latency (a graph is a few KiB):
+// k_sched_one + k_emit took 6.6 + 4.0 us on a tree of 16 prompts and 14.4 + 7 us on 64 merged graphs,
+// the wide kernel takes 8.2 and 16.9 (a decode step of one small prompt 21.4 -> 20.1 us).
+// A graph of up to kWideSegs segments leaves room in LDS for the offsets that k_emit would read.
 constexpr int kSmallSegs = 4096;
 constexpr int kSmallEntries = 8192;
 constexpr int kSmallBranches = 4096;
+constexpr int kWideSegs = 2048;
+constexpr int kWideBranches = 2048;
+constexpr int kWideGrid = 128;                   // most workgroups: a CU each
+constexpr int kWideItems = 512;                  // most items of a workgroup
 
 // reuse: the plan's groups are already in place from an earlier schedule (B(s), |B(s)|, the
 // group offsets, each entry's branch and rank, each group's branches in ascending order: they
 // follow the paths alone, which a plan keeps); only what the lengths decide is recomputed.
+template <bool WIDE>
 __global__ __launch_bounds__(1024) void k_sched_one(DevGraph g, DevSchedule sc, int32_t group,
                                                     int32_t chunk_pages, int32_t reuse) {
   constexpr int NBK = kCostClasses;
-  constexpr int SPT = kSmallSegs / 1024;
+  constexpr int kSegs = WIDE ? kWideSegs : kSmallSegs;
+  constexpr int kBranches = WIDE ? kWideBranches : kSmallBranches;
+  constexpr int SPT = kSegs / 1024;
   __shared__ unsigned short l_segs[kSmallEntries];        // path_segs
   __shared__ unsigned short l_tmp[kSmallEntries];         // B(s) in arrival order
-  __shared__ unsigned short l_poff[kSmallBranches + 1];   // path_off
-  __shared__ int l_npg[kSmallSegs];                       // pages in use per segment
-  __shared__ int l_nch[kSmallSegs];                       // chunks per segment
+  __shared__ unsigned short l_poff[kBranches + 1];   // path_off
+  __shared__ int l_npg[kSegs];                       // pages in use per segment
+  __shared__ int l_nch[kSegs];                       // chunks per segment
   __shared__ int l_part[kSmallEntries];                   // each entry's first partial slot
-  __shared__ int l_cnt[kSmallSegs];                       // |B(s)|
-  __shared__ int l_cur[kSmallSegs];                       // scatter cursors, then work-list order
+  __shared__ int l_cnt[kSegs];                       // |B(s)|
+  __shared__ int l_cur[kSegs];                       // scatter cursors, then work-list order
   __shared__ int l_cw[NBK * 4 * 16];                      // sort: counts per (class, slot, wave)
   __shared__ int l_boff[NBK];                             // sort: first position of each class
   __shared__ int l_wsum[2][3][16];                        // wave totals of the two block scans
+  __shared__ int l_goff[WIDE ? kSegs : 1];                 // group offsets
+  __shared__ int l_prow[WIDE ? kSegs : 1];                // first partial rows
+  __shared__ int l_ioff[WIDE ? kSegs : 1];                // first work items
+  __shared__ unsigned short l_br[WIDE ? kSmallEntries : 1];   // each entry's branch
+  __shared__ int2 l_items[WIDE ? kWideItems : 1];         // this workgroup's (segment, item of it)
   int* const l_order = l_cur;
+  const bool lead = !WIDE || blockIdx.x == 0;             // writes the per-segment outputs
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int S = g.S, E = g.E, B = g.B;
   const int per = (S + 1023) >> 10;
@@ -472,23 +529,28 @@ __global__ __launch_bounds__(1024) void k_sched_one(DevGraph g, DevSchedule sc, 
     }
   };
 
+  int vpage[SPT];                                  // (WIDE) page offsets, kept until their place
+                                                   // in LDS (the sort's counts) is free
   // 0. Read the graph (all loads issued before any is used); clear the counts and the sort's
   //    bins.
   {
-    int vs[kSmallEntries / 1024], vp[kSmallBranches / 1024], vl[SPT];
+    int vs[kSmallEntries / 1024], vp[kBranches / 1024], vl[SPT];
 #pragma unroll
     for (int u = 0; u < kSmallEntries / 1024; ++u)
       vs[u] = t + 1024 * u < E ? g.path_segs[t + 1024 * u] : 0;
 #pragma unroll
-    for (int u = 0; u < kSmallBranches / 1024; ++u)
+    for (int u = 0; u < kBranches / 1024; ++u)
       vp[u] = t + 1024 * u <= B ? (int)g.path_off[t + 1024 * u] : 0;
 #pragma unroll
-    for (int u = 0; u < SPT; ++u) vl[u] = t + 1024 * u < S ? g.seg_len[t + 1024 * u] : 0;
+    for (int u = 0; u < SPT; ++u) {
+      vl[u] = t + 1024 * u < S ? g.seg_len[t + 1024 * u] : 0;
+      if constexpr (WIDE) vpage[u] = t + 1024 * u < S ? (int)g.seg_page_off[t + 1024 * u] : 0;
+    }
 #pragma unroll
     for (int u = 0; u < kSmallEntries / 1024; ++u)
       if (t + 1024 * u < E) l_segs[t + 1024 * u] = (unsigned short)vs[u];
 #pragma unroll
-    for (int u = 0; u < kSmallBranches / 1024; ++u)
+    for (int u = 0; u < kBranches / 1024; ++u)
       if (t + 1024 * u <= B) l_poff[t + 1024 * u] = (unsigned short)vp[u];
 #pragma unroll
     for (int u = 0; u < SPT; ++u)
@@ -508,7 +570,7 @@ __global__ __launch_bounds__(1024) void k_sched_one(DevGraph g, DevSchedule sc, 
     }
     for (int i = t; i < 4 * 16 * NBK; i += 1024) l_cw[i] = 0;
   }
-  if (t < kNumCounters) sc.counters[t] = 0;
+  if (lead && t >= 2 && t < kNumCounters) sc.counters[t] = 0;   // (0 and 1 are written below)
   lds_barrier();
 
   // 1. |B(s)|, and the chunks of the entries of this thread's branches (one partial row per
@@ -542,18 +604,25 @@ __global__ __launch_bounds__(1024) void k_sched_one(DevGraph g, DevSchedule sc, 
         const int nch = cnt > 0 ? nch_len(s) : 0;
         if (!reuse) {
           l_cur[s] = ra;
-          sc.grp_cnt[s] = cnt;
-          sc.grp_off[s] = ra;
+          if (lead) {
+            sc.grp_cnt[s] = cnt;
+            sc.grp_off[s] = ra;
+          }
         }
-        sc.seg_prow_off[s] = rc;
-        sc.seg_nchunk[s] = nch;
+        if constexpr (WIDE) {
+          l_goff[s] = ra;
+          l_prow[s] = rc;
+        } else {
+          sc.seg_prow_off[s] = rc;
+        }
+        if (lead) sc.seg_nchunk[s] = nch;
         ra += cnt;
         rc += nch * cnt;
       }
     }
-    if (t == 1023) {
+    if (t == 1023 && lead) {
       if (!reuse) sc.grp_off[S] = tot[0];
-      sc.seg_prow_off[S] = tot[2];
+      if (!WIDE) sc.seg_prow_off[S] = tot[2];
       sc.counters[1] = tot[2];
       sc.bpart_off[B] = tot[1];
     }
@@ -616,14 +685,15 @@ __global__ __launch_bounds__(1024) void k_sched_one(DevGraph g, DevSchedule sc, 
   {
     int slot = slot0;
     for (int b = b0; b < b1; ++b) {
-      sc.bpart_off[b] = slot;
+      if (lead) sc.bpart_off[b] = slot;
       for (int e = l_poff[b]; e < l_poff[b + 1]; ++e) {
-        if (!reuse) sc.entry_branch[e] = b;
+        if constexpr (WIDE) l_br[e] = (unsigned short)b;
+        else if (!reuse) sc.entry_branch[e] = b;
         l_part[e] = slot;                          // (written out coalesced after the barrier)
         slot += nch_len(l_segs[e]);
       }
     }
-    if (!reuse)
+    if (!WIDE && !reuse)
       for (int e = t; e < E; e += 1024) sc.grp_tmp[e] = l_tmp[e];
   }
   if (wv == 0) {
@@ -634,7 +704,8 @@ __global__ __launch_bounds__(1024) void k_sched_one(DevGraph g, DevSchedule sc, 
   lds_barrier();
 
   // 5. Place each segment at its work-list position; the entries' first partial slots.
-  for (int e = t; e < E; e += 1024) sc.entry_part[e] = l_part[e];
+  if (!WIDE)
+    for (int e = t; e < E; e += 1024) sc.entry_part[e] = l_part[e];
 #pragma unroll
   for (int u = 0; u < SPT; ++u) {
     const int sg = 1024 * u + t;
@@ -652,6 +723,49 @@ __global__ __launch_bounds__(1024) void k_sched_one(DevGraph g, DevSchedule sc, 
     const int own = v[0];
     block_scan3(v, l_wsum[1], tot);
     int w = v[0] - own;
+    if constexpr (WIDE) {
+      static_assert(NBK * 4 * 16 >= kSegs, "page offsets take the place of the sort's counts");
+#pragma unroll
+      for (int u = 0; u < SPT; ++u) l_cw[1024 * u + t] = vpage[u];
+      const int share = (tot[0] + (int)gridDim.x - 1) / (int)gridDim.x;   // <= kWideItems
+      const int w0 = min(tot[0], (int)blockIdx.x * share), w1 = min(tot[0], w0 + share);
+      for (int i = s0; i < s1; ++i) {
+        const int s = l_order[i];
+        const int nit = l_cnt[s] > 0 ? nch_len(s) * nrb_of(s) : 0;
+        l_ioff[s] = w;
+        for (int k = max(0, w0 - w); k < min(nit, w1 - w); ++k)
+          l_items[w + k - w0] = make_int2(s, k);
+        w += nit;
+      }
+      if (t == 1023 && lead) sc.counters[0] = tot[0];
+      lds_barrier();
+      // 7. This workgroup's path entries: rank, partial rows, the branch's place in descriptors.
+      for (int e = (int)blockIdx.x * 1024 + t; e < E; e += (int)gridDim.x * 1024) {
+        const int b = l_br[e], s = l_segs[e];
+        int rank = 0;
+        if (reuse) {
+          rank = sc.entry_rank[e];
+        } else {
+          const int off = l_goff[s], cnt = l_cnt[s];
+#pragma unroll 8
+          for (int k = 0; k < cnt; ++k) rank += l_tmp[off + k] < b;
+          sc.grp_br[off + rank] = b;
+          sc.entry_rank[e] = rank;
+        }
+        emit_entry(sc, group, chunk_pages, b, rank, l_cnt[s], nch_len(s), l_part[e], l_prow[s],
+                   l_ioff[s]);
+      }
+      // 8. Its items, a wave each: descriptor head and page ids.
+      for (int j = wv; j < w1 - w0; j += 16) {
+        const int s = __builtin_amdgcn_readfirstlane(l_items[j].x);
+        const int k = __builtin_amdgcn_readfirstlane(l_items[j].y);
+        const int nrb = nrb_of(s), c = k / nrb, rb = k - c * nrb;
+        if (lane == 0) sc.items[w0 + j] = make_int4(s, c, rb, 0);
+        emit_item(g, sc, w0 + j, s, c, rb, npg_of(s), nch_len(s), l_cnt[s], l_goff[s], l_prow[s],
+                  l_cw[s], lane);
+      }
+      return;
+    }
 #pragma unroll
     for (int u = 0; u < SPT; ++u) {
       const int i = s0 + u;
@@ -704,41 +818,17 @@ __global__ __launch_bounds__(kT) void k_emit(DevGraph g, DevSchedule sc, int32_t
       sc.grp_br[off + r] = b;
       sc.entry_rank[e] = r;
     }
-    const int nch = sc.seg_nchunk[s];
-    const int slot = (int)sc.entry_part[e];
-    const int prow = (int)sc.seg_prow_off[s] + r;
-    for (int c = 0; c < nch; ++c) sc.bpart[slot + c] = prow + c * cnt;
-    const int nrb = (cnt * group + kRowsPerBlock - 1) / kRowsPerBlock;
-    const int rb_lo = (r * group) / kRowsPerBlock;
-    const int rb_hi = (r * group + group - 1) / kRowsPerBlock;
-    const int w0 = (int)sc.seg_item_off[s];
-    for (int c = 0; c < nch; ++c)
-      for (int rb = rb_lo; rb <= rb_hi; ++rb) {
-        const int64_t w = w0 + c * nrb + rb;
-        const int j0 = (rb * kRowsPerBlock) / group;
-        sc.desc[w * sc.desc_words + kDescHead + chunk_pages + (r - j0)] = b;
-      }
+    emit_entry(sc, group, chunk_pages, b, r, cnt, sc.seg_nchunk[s], (int)sc.entry_part[e],
+               (int)sc.seg_prow_off[s], (int)sc.seg_item_off[s]);
     return;
   }
   const int64_t w = (int64_t)(blockIdx.x - eblocks) * (kT / 64) + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
   if (w >= sc.counters[0]) return;
   const int4 it = sc.items[w];
-  const int s = it.x, c = it.y, rb = it.z;
-  const int cnt = sc.grp_cnt[s], len = g.seg_len[s];
-  const int npg = (len + kPageTokens - 1) / kPageTokens;
-  const int nch = (npg + chunk_pages - 1) / chunk_pages;
-  const int p0 = chunk_first_page(c, npg, nch);
-  const int np = chunk_first_page(c + 1, npg, nch) - p0;
-  const int poff = (int)g.seg_page_off[s] + p0;
-  int32_t* d = sc.desc + w * sc.desc_words;
-  if (lane == 0) {
-    reinterpret_cast<int4*>(d)[0] =
-        make_int4(np, causal_word(g, s, p0), len - (npg - 1) * kPageTokens, cnt);
-    reinterpret_cast<int4*>(d)[1] =
-        make_int4(rb, (int)sc.grp_off[s], poff, (int)sc.seg_prow_off[s] + c * cnt);
-  }
-  for (int i = lane; i < np; i += 64) d[kDescHead + i] = g.seg_pages[poff + i];
+  const int s = it.x;
+  const int npg = (g.seg_len[s] + kPageTokens - 1) / kPageTokens;
+  emit_item(g, sc, w, s, it.y, it.z, npg, (npg + chunk_pages - 1) / chunk_pages, sc.grp_cnt[s],
+            (int)sc.grp_off[s], (int)sc.seg_prow_off[s], (int)g.seg_page_off[s], threadIdx.x & 63);
 }
 
 __global__ void k_scatter(DevGraph g, DevSchedule sc) {
@@ -857,7 +947,16 @@ hipError_t launch_schedule(const DevGraph& g, const DevSchedule& sc, int32_t gro
                            hipStream_t stream) {
   const int fill_blocks = (int)((max_items + kT / 64 - 1) / (kT / 64));
   if (g.S <= kSmallSegs && g.E <= kSmallEntries && g.B < kSmallBranches) {
-    hipLaunchKernelGGL(k_sched_one, dim3(1), dim3(1024), 0, stream, g, sc, group, chunk_pages,
+    // Wide where its LDS holds the graph: a wave for each item up to kWideGrid workgroups (the
+    // entries then spread over the same ones), as long as a workgroup's share fits its list.
+    if (g.S <= kWideSegs && g.B < kWideBranches && max_items <= (int64_t)kWideGrid * kWideItems) {
+      const int64_t want = max_items / 16 + 1;
+      const int wide = (int)(want < kWideGrid ? want : kWideGrid);
+      hipLaunchKernelGGL(k_sched_one<true>, dim3(wide), dim3(1024), 0, stream, g, sc, group,
+                         chunk_pages, (int32_t)reuse);
+      return hipGetLastError();
+    }
+    hipLaunchKernelGGL(k_sched_one<false>, dim3(1), dim3(1024), 0, stream, g, sc, group, chunk_pages,
                        (int32_t)reuse);
     const int eblocks = blocks(g.E);
     if (eblocks + fill_blocks > 0)

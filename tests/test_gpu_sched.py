@@ -214,3 +214,30 @@ def test_chains_past_the_counting_sort(n):
     assert len(chains(g)) == n + 1 > 4096
     check_schedule(wl)
     check_workload(wl, branches=[0, 1, n // 2, n - 2, n - 1], out_f32=True)
+
+
+@pytest.mark.parametrize("n", [1, 3, 1023, 2046, 2047, 2048, 4000])
+def test_wide_scheduler_edges(n):
+    """A root shared by n branches with a segment of their own each: 2,047 branches and 2,048
+    chains are the most that the wide scheduler (every workgroup schedules, then writes its share)
+    takes; beyond them one workgroup schedules and a second kernel writes."""
+    rng = np.random.default_rng(n)
+    lens = [900] + [int(x) for x in rng.integers(1, 90, size=n)]
+    g = W.assemble_graph(lens, [[0, 1 + i] for i in range(n)], 5)
+    check_schedule(W.make_workload(f"{n}-way fan", g, 28, 4, 64, "bf16", 5))
+
+
+def test_more_items_than_the_wide_scheduler_lists():
+    """2,000 branches of 32 q-heads on one kv-head share 400,000 tokens: 500 row blocks of each
+    chunk make more items than 128 workgroups list (65,536), which takes the other path."""
+    n = 2000
+    g = W.assemble_graph([400_000] + [3] * n, [[0, 1 + i] for i in range(n)], 5)
+    hg = G.HostGraph.from_graph(g)
+    p = G.make_params(32, 1, 64, g.num_pages, "bf16")
+    with G.Plan(hg, p) as plan:
+        plan.schedule()
+        d, info = plan.debug_dump(), plan.info()
+        say(f"[case] {len(d['items'])} items, {info.chunk_pages} pages a chunk")
+        offs, _ = O.segment_groups(g.path_offsets, g.path_segs, g.num_segments)
+        assert len(d["items"]) > 65536
+        assert np.array_equal(d["items"], expected_items(g, 32, info.chunk_pages, np.diff(offs)))
