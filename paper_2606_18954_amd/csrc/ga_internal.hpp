@@ -225,6 +225,8 @@ struct LengthArgs {
   int32_t* chain_causal;           // [chains] written for multi-query plans (DevGraph::seg_causal)
 };
 hipError_t launch_set_lengths(const LengthArgs& a, hipStream_t stream);
+// src is pinned host memory; both 16-byte aligned.
+hipError_t launch_upload(void* dst, const void* src, size_t bytes, hipStream_t stream);
 
 // reuse: the groups (B(s), |B(s)|, entry branches and ranks, ascending group lists) written by
 // an earlier schedule of the same plan are still in place, and only what the lengths decide is
