@@ -274,7 +274,6 @@ __global__ __launch_bounds__(NT) void k_prompt_advantages(RewardArgs a, int cap)
   u16* s_cpos = s_cdep + cap;                                      // [cap + 1]
   const int2 pr = a.prompts[blockIdx.x];
   const int s0 = pr.x, n = pr.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int t0 = a.tin[s0];
   for (int v = tid; v <= n; v += NT) {
     s_off[v] = 0;
     if (v < n) s_ctot[v] = 0;
@@ -286,13 +285,15 @@ __global__ __launch_bounds__(NT) void k_prompt_advantages(RewardArgs a, int cap)
     const int l = a.labels[g];
     const int lab = ((l >= s0 && l <= g) ? l : g) - s0;
     const int p = a.parent[g];
-    const int tin = a.tin[g] - t0;
+    const int tin = a.tin[g] - s0;                   // (the walk numbers every prompt's states in
+                                                     // turn, so its root's number is its id)
     const int r = a.reward[g];
     s_lab[v] = (u16)lab;
     s_par[v] = p >= 0 ? (u16)(p - s0) : kNone;
     s_dep[v] = (u16)a.depth[g];
     s_tin[v] = (u16)tin;
-    s_tout[v] = (u16)(a.tout[g] - t0);
+    s_tout[v] = (u16)(a.tout[g] - s0);
+    s_r[v] = (double)a.edge_sim[g];                  // (until the step rewards take their place)
     s_eul[tin] = (u16)v;
     s_pre[tin] = r >= 0 ? (((long long)r << 32) | 1) : 0;
     if (p >= 0) s_kids[v] = (u16)(atomicAdd(&s_off[p - s0], 1u) & 0xffff);
@@ -379,7 +380,7 @@ __global__ __launch_bounds__(NT) void k_prompt_advantages(RewardArgs a, int cap)
   for (int v = tid; v < n; v += NT) {                // step rewards; class efficiency values
     const int p = s_par[v];
     double r = __builtin_nan("");
-    if (p != kNone) r = (s_S[v] - s_S[p]) * (1.0 - fmax(0.0, (double)a.edge_sim[s0 + v]));
+    if (p != kNone) r = (s_S[v] - s_S[p]) * (1.0 - fmax(0.0, s_r[v]));
     s_r[v] = r;
     a.step[s0 + v] = r;
     const u16* mem = s_mem + mem0(v);
@@ -488,7 +489,7 @@ __global__ __launch_bounds__(NT) void k_prompt_advantages(RewardArgs a, int cap)
       for (int k = s_cpos[s_tin[u]]; k < c1; ++k)
         if (s_cdep[k] < du) e += s_cval[k];
     }
-    a.a_eff[s0 + u] = e;
+    s_aen[u] = e;                                    // (aen was last read by the compaction)
   }
   __syncthreads();
   for (int v = tid; v < n; v += NT) {
@@ -496,7 +497,8 @@ __global__ __launch_bounds__(NT) void k_prompt_advantages(RewardArgs a, int cap)
     double c = 0.0;
     if (p != kNone && !isnan(s_r[v]) && s_gs[p] > 0.0) c = (s_r[v] - s_gm[p]) / s_gs[p];
     a.a_cor[s0 + v] = c;
-    a.a_dual[s0 + v] = c + a.lambda_eff * a.a_eff[s0 + v];   // written by this thread above
+    a.a_eff[s0 + v] = s_aen[v];
+    a.a_dual[s0 + v] = c + a.lambda_eff * s_aen[v];
   }
 }
 
