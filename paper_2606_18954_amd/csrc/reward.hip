@@ -229,14 +229,15 @@ __global__ void k_dual(RewardArgs a) {
 //   outcomes   a prefix sum of the packed (R, 1) values in Euler order (subtrees are ranges);
 //   pooling    class totals by LDS integer atomics;
 //   lists      children and class members as CSR, a state's place in its list being the number
-//              of smaller ids there, so each state's correctness group reads only its class's
-//              children (and only states with children have a group that is read) and each
-//              class's efficiency values only its members;
+//              of smaller ids there; step rewards are kept at those places, so a state's
+//              correctness group reads runs of its class's children's (and only states with
+//              children have a group that is read), and a class's smallest member only its
+//              members (their common ancestor is that of the first and last in Euler order);
 //   routes     the edge into u sums over u's subtree: a range of the Euler order, of which only
 //              the members of classes with an anchor are kept (in that order).
 // The results equal the multi-kernel path's up to the order of a few fp64 sums.
-//   512 prompts of 205 states: 49 -> 30 us; 64 prompts of 517 states, which took the multi-kernel
-//   path's scans of the whole prompt per state: 585 -> 23 us.
+//   512 prompts of 205 states: 49 -> 21 us; 64 prompts of 517 states, which took the multi-kernel
+//   path's scans of the whole prompt per state: 585 -> 17 us.
 // Indices are prompt-local and held in 16 bits; LDS is sized for the batch's largest prompt.
 __host__ __device__ constexpr size_t reward_lds_bytes(int n) {
   return 8 * (size_t)(5 * n + 1) + 4 * (size_t)(n + 1) + 2 * (size_t)(13 * n + 1);
@@ -293,7 +294,7 @@ __global__ __launch_bounds__(NT) void k_prompt_advantages(RewardArgs a, int cap)
     s_dep[v] = (u16)a.depth[g];
     s_tin[v] = (u16)tin;
     s_tout[v] = (u16)(a.tout[g] - s0);
-    s_r[v] = (double)a.edge_sim[g];                  // (until the step rewards take their place)
+    s_aen[v] = (double)a.edge_sim[g];                // (until the classes' values take its place)
     s_eul[tin] = (u16)v;
     s_pre[tin] = r >= 0 ? (((long long)r << 32) | 1) : 0;
     if (p >= 0) s_kids[v] = (u16)(atomicAdd(&s_off[p - s0], 1u) & 0xffff);
@@ -361,7 +362,7 @@ __global__ __launch_bounds__(NT) void k_prompt_advantages(RewardArgs a, int cap)
       const int k0 = kid0(p), k1 = kid1(p);
       int at = k0;
       for (int k = k0; k < k1; ++k) at += s_ku[k] < v;
-      s_kids[at] = (u16)v;
+      s_kids[v] = (u16)at;
     }
     const int m0 = mem0(l), m1 = mem1(l);
     int at = m0;
@@ -377,59 +378,65 @@ __global__ __launch_bounds__(NT) void k_prompt_advantages(RewardArgs a, int cap)
     a.score[s0 + v] = S;
   }
   __syncthreads();
-  for (int v = tid; v < n; v += NT) {                // step rewards; class efficiency values
+  // Step rewards, at the states' places in their predecessors' lists; and per class of two and more,
+  // by its smallest member, what its members' efficiency values are made of: the gate (in aen), the
+  // route lengths' mean and deviation (in gm and gs) and the anchor.
+  for (int v = tid; v < n; v += NT) {
     const int p = s_par[v];
     double r = __builtin_nan("");
-    if (p != kNone) r = (s_S[v] - s_S[p]) * (1.0 - fmax(0.0, s_r[v]));
-    s_r[v] = r;
+    if (p != kNone) {
+      r = (s_S[v] - s_S[p]) * (1.0 - fmax(0.0, s_aen[v]));
+      s_r[s_kids[v]] = r;
+    }
     a.step[s0 + v] = r;
     const u16* mem = s_mem + mem0(v);
     const int m = mem1(v) - mem0(v);
     if (s_lab[v] != v || m < 2) continue;
-    int lca = mem[0], sdef = 0;
+    // The lowest common ancestor of a set is that of its first and last state in Euler order.
+    int sdef = 0, dsum = 0, first = n, last = 0;
     double ssum = 0.0;
+#pragma unroll 4
     for (int k = 0; k < m; ++k) {
-      const int x = mem[k];
-      if (!isnan(s_S[x])) {
-        ssum += s_S[x];
-        ++sdef;
-      }
-      int y = x, z = lca;                            // lowest common ancestor by depth walking
-      while (s_dep[y] > s_dep[z]) y = s_par[y];
-      while (s_dep[z] > s_dep[y]) z = s_par[z];
-      while (y != z) {
-        y = s_par[y];
-        z = s_par[z];
-      }
-      lca = y;
+      const int x = mem[k], t = s_tin[x];
+      const double S = s_S[x];
+      ssum += isnan(S) ? 0.0 : S;
+      sdef += !isnan(S);
+      dsum += s_dep[x];
+      first = min(first, t);
+      last = max(last, t);
     }
-    const int anc = s_lab[lca] == v ? s_par[lca] : lca;
+    int y = s_eul[first], z = s_eul[last];
+    while (s_dep[y] > s_dep[z]) y = s_par[y];        // (by depth walking)
+    while (s_dep[z] > s_dep[y]) z = s_par[z];
+    while (y != z) {
+      y = s_par[y];
+      z = s_par[z];
+    }
+    const int anc = s_lab[y] == v ? s_par[y] : y;
     if (anc == kNone) continue;                      // a class holding its prompt's root
-    const double gate = sdef > 0 ? ssum / sdef : 0.0;
-    double lsum = 0.0;
-    for (int k = 0; k < m; ++k) lsum += -(double)(s_dep[mem[k]] - s_dep[anc]);
-    const double mean = lsum / m;
+    const int da = s_dep[anc];
+    const double mean = -(double)(dsum - m * da) / m;
     double q = 0.0;
+#pragma unroll 4
     for (int k = 0; k < m; ++k) {
-      const double d = -(double)(s_dep[mem[k]] - s_dep[anc]) - mean;
+      const double d = -(double)(s_dep[mem[k]] - da) - mean;
       q += d * d;
     }
-    const double sd = sqrt(q / m);
-    for (int k = 0; k < m; ++k) {
-      const int x = mem[k];
-      const double l = -(double)(s_dep[x] - s_dep[anc]);
-      s_aen[x] = sd > 0.0 ? gate * (l - mean) / sd : 0.0;
-      s_anc[x] = (u16)anc;
-    }
+    s_aen[v] = sdef > 0 ? ssum / sdef : 0.0;
+    s_gm[v] = mean;
+    s_gs[v] = sqrt(q / m);
+    s_anc[v] = (u16)anc;
   }
   __syncthreads();
-  // The Euler order's class members with an anchor, and how many lie before each position.
+  // The efficiency values and anchors' depths of the class members with an anchor, in Euler order,
+  // and how many lie before each position.
   {
     unsigned carry = 0;
     for (int b0 = 0; b0 <= n; b0 += NT) {
       const int i = b0 + tid;
       const int x = i < n ? s_eul[i] : 0;
-      const bool on = i < n && s_anc[x] != kNone;
+      const int l = s_lab[x], anc = s_anc[l];
+      const bool on = i < n && anc != kNone;
       const unsigned long long bal = __ballot(on);
       if (lane == 0) s_wcnt[wave] = (unsigned)__popcll(bal);
       __syncthreads();
@@ -441,8 +448,9 @@ __global__ __launch_bounds__(NT) void k_prompt_advantages(RewardArgs a, int cap)
       at += (unsigned)__popcll(bal & ((1ull << lane) - 1));
       if (i <= n) s_cpos[i] = (u16)at;
       if (on) {
-        s_cval[at] = s_aen[x];
-        s_cdep[at] = s_dep[s_anc[x]];
+        const double len = -(double)(s_dep[x] - s_dep[anc]), sd = s_gs[l];
+        s_cval[at] = sd > 0.0 ? s_aen[l] * (len - s_gm[l]) / sd : 0.0;
+        s_cdep[at] = s_dep[anc];
       }
       __syncthreads();
     }
@@ -455,12 +463,12 @@ __global__ __launch_bounds__(NT) void k_prompt_advantages(RewardArgs a, int cap)
       for (int k = m0; k < m1; ++k) {
         const int q = s_mem[k], k1 = kid1(q);
         if (q != u && s_dep[q] < du) continue;       // (its children lie no deeper than u)
+        members += k1 - kid0(q);
+#pragma unroll 4
         for (int j = kid0(q); j < k1; ++j) {
-          const double r = s_r[s_kids[j]];
-          ++members;
-          if (isnan(r)) continue;
-          sum += r;
-          ++cnt;
+          const double r = s_r[j];
+          sum += isnan(r) ? 0.0 : r;
+          cnt += !isnan(r);
         }
       }
       double mean = 0.0, sd = 0.0;
@@ -470,10 +478,9 @@ __global__ __launch_bounds__(NT) void k_prompt_advantages(RewardArgs a, int cap)
         for (int k = m0; k < m1; ++k) {
           const int q = s_mem[k], k1 = kid1(q);
           if (q != u && s_dep[q] < du) continue;
+#pragma unroll 4
           for (int j = kid0(q); j < k1; ++j) {
-            const double r = s_r[s_kids[j]];
-            if (isnan(r)) continue;
-            const double d = r - mean;
+            const double r = s_r[j], d = isnan(r) ? 0.0 : r - mean;
             q2 += d * d;
           }
         }
@@ -486,8 +493,11 @@ __global__ __launch_bounds__(NT) void k_prompt_advantages(RewardArgs a, int cap)
     double e = 0.0;
     if (s_par[u] != kNone) {
       const int du = s_dep[u], c1 = s_cpos[s_tout[u]];
-      for (int k = s_cpos[s_tin[u]]; k < c1; ++k)
-        if (s_cdep[k] < du) e += s_cval[k];
+#pragma unroll 4
+      for (int k = s_cpos[s_tin[u]]; k < c1; ++k) {
+        const double x = s_cval[k];
+        e += s_cdep[k] < du ? x : 0.0;
+      }
     }
     s_aen[u] = e;                                    // (aen was last read by the compaction)
   }
@@ -495,7 +505,10 @@ __global__ __launch_bounds__(NT) void k_prompt_advantages(RewardArgs a, int cap)
   for (int v = tid; v < n; v += NT) {
     const int p = s_par[v];
     double c = 0.0;
-    if (p != kNone && !isnan(s_r[v]) && s_gs[p] > 0.0) c = (s_r[v] - s_gm[p]) / s_gs[p];
+    if (p != kNone && s_gs[p] > 0.0) {
+      const double r = s_r[s_kids[v]];
+      if (!isnan(r)) c = (r - s_gm[p]) / s_gs[p];
+    }
     a.a_cor[s0 + v] = c;
     a.a_eff[s0 + v] = s_aen[v];
     a.a_dual[s0 + v] = c + a.lambda_eff * s_aen[v];
