@@ -679,6 +679,16 @@ ga_status plan_init(const ga_segment_table* st, const ga_branch_paths* bp, const
 // both are bound by the host link.
 constexpr size_t kKernelUploadBytes = size_t(1) << 20;
 
+// src: pinned host memory; both 16-byte aligned.
+__global__ __launch_bounds__(256) void k_upload(char* dst, const char* src, int64_t bytes) {
+  const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 16;
+  if (i + 16 <= bytes) {
+    *reinterpret_cast<uint4*>(dst + i) = *reinterpret_cast<const uint4*>(src + i);
+  } else {
+    for (int64_t k = i; k < bytes; ++k) dst[k] = src[k];
+  }
+}
+
 ga_status upload(ga_plan* pl, const Layout& L, bool pinned, hipStream_t stream) {
   const CGraph& c = pl->cg;
   const ga_segment_table cst{pl->z.S, c.seg_len.data(), c.seg_page_off.data(), c.seg_pages.data()};
@@ -700,10 +710,14 @@ ga_status upload(ga_plan* pl, const Layout& L, bool pinned, hipStream_t stream) 
   pl->h_pages.clear();
   pl->h_pages.shrink_to_fit();
   const size_t bytes = upload_bytes(L);
-  if (pinned && bytes <= kKernelUploadBytes)
-    GA_HIP(ga::launch_upload(pl->dev, pl->pin, bytes, stream), "graph upload");
-  else
+  if (pinned && bytes > 0 && bytes <= kKernelUploadBytes) {
+    hipLaunchKernelGGL(k_upload, dim3((unsigned)((bytes + 16 * 256 - 1) / (16 * 256))), dim3(256), 0,
+                       stream, static_cast<char*>(pl->dev), static_cast<const char*>(pl->pin),
+                       (int64_t)bytes);
+    GA_HIP(hipGetLastError(), "graph upload");
+  } else {
     GA_HIP(hipMemcpyAsync(pl->dev, pl->pin, bytes, hipMemcpyHostToDevice, stream), "graph upload");
+  }
   if (pl->uploaded) GA_HIP(hipEventRecord(pl->uploaded, stream), "record upload");
   return GA_OK;
 }

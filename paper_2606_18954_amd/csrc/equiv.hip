@@ -654,13 +654,20 @@ hipError_t launch_equivalence(const EquivArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_suffix(SuffixArgs a, hipStream_t stream) {
-  if (a.N == 0) return hipSuccess;
+hipError_t launch_suffix_count(const SuffixArgs& args, hipStream_t stream) {
+  if (args.N == 0) return hipSuccess;
+  SuffixArgs a = args;
   a.nblk = (a.N + kSufBlock - 1) / kSufBlock;
-  const dim3 grid((unsigned)a.nblk);
-  hipLaunchKernelGGL(k_suffix<false>, grid, dim3(kSufBlock), 0, stream, a);
+  hipLaunchKernelGGL(k_suffix<false>, dim3((unsigned)a.nblk), dim3(kSufBlock), 0, stream, a);
   if (a.nblk > kSufDirect) hipLaunchKernelGGL(k_suffix_blocks, dim3(1), dim3(1024), 0, stream, a);
-  hipLaunchKernelGGL(k_suffix<true>, grid, dim3(kSufBlock), 0, stream, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_suffix_fill(const SuffixArgs& args, hipStream_t stream) {
+  if (args.N == 0) return hipSuccess;
+  SuffixArgs a = args;
+  a.nblk = (a.N + kSufBlock - 1) / kSufBlock;
+  hipLaunchKernelGGL(k_suffix<true>, dim3((unsigned)a.nblk), dim3(kSufBlock), 0, stream, a);
   return hipGetLastError();
 }
 

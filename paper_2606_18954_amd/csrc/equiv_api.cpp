@@ -355,7 +355,8 @@ ga_status forest_suffix(ga_forest* f, const int32_t* labels, int64_t* suffix_off
   a.capacity = capacity;
   a.N = N;
   *f->total = 0;
-  if (N > 0) EQ_HIP(ga::launch_suffix(a, stream), "suffix launch");
+  EQ_HIP(ga::launch_suffix_count(a, stream), "suffix count launch");
+  EQ_HIP(ga::launch_suffix_fill(a, stream), "suffix fill launch");
   EQ_HIP(hipStreamSynchronize(stream), "synchronise");
   const int64_t n = *static_cast<volatile int64_t*>(f->total);
   *total = n;

@@ -173,7 +173,7 @@ struct SuffixArgs {
   int64_t* total;          // entries of the lists (pinned host memory)
   int64_t capacity;        // offsets and lists are written only if they fit
   int64_t N;
-  int64_t nblk;            // (set by the launcher)
+  int64_t nblk;            // (set by the launchers)
 };
 
 // States of a prompt whose rewards one workgroup computes: its arrays (70 bytes a state) then fit
@@ -225,8 +225,6 @@ struct LengthArgs {
   int32_t* chain_causal;           // [chains] written for multi-query plans (DevGraph::seg_causal)
 };
 hipError_t launch_set_lengths(const LengthArgs& a, hipStream_t stream);
-// src is pinned host memory; both 16-byte aligned.
-hipError_t launch_upload(void* dst, const void* src, size_t bytes, hipStream_t stream);
 
 // reuse: the groups (B(s), |B(s)|, entry branches and ranks, ascending group lists) written by
 // an earlier schedule of the same plan are still in place, and only what the lengths decide is
@@ -246,7 +244,8 @@ hipError_t launch_merge(const MergeArgs& a, int head_dim, bool out_bf16, bool pa
                         hipStream_t stream, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
 hipError_t launch_kv_write(const KvWriteArgs& a, hipStream_t stream);
 hipError_t launch_equivalence(const EquivArgs& a, hipStream_t stream);
-hipError_t launch_suffix(SuffixArgs a, hipStream_t stream);
+hipError_t launch_suffix_count(const SuffixArgs& a, hipStream_t stream);
+hipError_t launch_suffix_fill(const SuffixArgs& a, hipStream_t stream);
 hipError_t launch_advantages(const RewardArgs& a, hipStream_t stream);
 // Number of co-resident attention workgroups the persistent grid uses on this device.
 int seg_attn_grid(int head_dim, bool bf16, bool causal, bool few_pages, int num_cus);

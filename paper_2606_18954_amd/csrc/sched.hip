@@ -942,24 +942,6 @@ hipError_t launch_set_lengths(const LengthArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// Host staging (pinned) -> plan workspace, read by the compute units over the host link.
-__global__ __launch_bounds__(kT) void k_upload(char* dst, const char* src, int64_t bytes) {
-  const int64_t i = ((int64_t)blockIdx.x * kT + threadIdx.x) * 16;
-  if (i + 16 <= bytes) {
-    *reinterpret_cast<uint4*>(dst + i) = *reinterpret_cast<const uint4*>(src + i);
-  } else {
-    for (int64_t k = i; k < bytes; ++k) dst[k] = src[k];
-  }
-}
-
-hipError_t launch_upload(void* dst, const void* src, size_t bytes, hipStream_t stream) {
-  if (bytes == 0) return hipSuccess;
-  const unsigned grid = (unsigned)((bytes + 16 * kT - 1) / (16 * kT));
-  hipLaunchKernelGGL(k_upload, dim3(grid), dim3(kT), 0, stream, static_cast<char*>(dst),
-                     static_cast<const char*>(src), (int64_t)bytes);
-  return hipGetLastError();
-}
-
 hipError_t launch_schedule(const DevGraph& g, const DevSchedule& sc, int32_t group,
                            int32_t chunk_pages, int64_t max_items, bool reuse,
                            hipStream_t stream) {
