@@ -64,9 +64,10 @@ __device__ void unite(int* rep, int a, int b) {
 // What bounds it: HBM (each embedding is read once), as long as LDS keeps up.  The upper triangle
 // of 64 x 64 blocks goes to the waves as whole blocks: waves 0 to 5 the six blocks off the
 // diagonal (16 tiles of 16 x 16 from 8 operand reads per stage), waves 6 and 7 two diagonal blocks
-// each (20 tiles from 8 reads), so a stage costs 64 KiB of LDS reads.  Row strips of single tiles
-// (17 tiles from 19 reads per wave, 152 KiB) were bound by them: 194 -> 182 us
-// for 512 prompts of 205 states and width 4096, and 165 us (5.2 TB/s) with the staggered start.
+// each (20 tiles from 8 reads), so a stage costs 64 KiB of LDS reads where row strips of single
+// tiles (17 tiles from 19 reads per wave) cost 152; and strips without states are not copied.  Both
+// together took a pass over 512 prompts of 205 states and width 4096 from 194 to 182 us, the
+// staggered start below to 165 us (5.2 TB/s).
 // The squared norms are the diagonals of the diagonal tiles (the same fp32 sums as the dot
 // products).  Links are made with a union-find in LDS and the labels written at the end.
 constexpr int kPromptMax = 256;
