@@ -354,11 +354,11 @@ ga_status forest_suffix(ga_forest* f, const int32_t* labels, int64_t* suffix_off
   a.total = f->total;
   a.capacity = capacity;
   a.N = N;
-  *f->total = 0;
   EQ_HIP(ga::launch_suffix_count(a, stream), "suffix count launch");
   EQ_HIP(ga::launch_suffix_fill(a, stream), "suffix fill launch");
   EQ_HIP(hipStreamSynchronize(stream), "synchronise");
-  const int64_t n = *static_cast<volatile int64_t*>(f->total);
+  // (the fill always writes it)
+  const int64_t n = N > 0 ? *static_cast<volatile int64_t*>(f->total) : 0;
   *total = n;
   if (n > capacity)
     return efail(GA_ERANGE, "graph suffix needs %lld entries, capacity is %lld", (long long)n,
