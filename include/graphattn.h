@@ -283,7 +283,8 @@ ga_status graphattn_forest_create(const ga_state_forest* forest, void* hip_strea
                                   ga_forest** out);
 /* forest_classes also writes, when edge_sim is not NULL, edge_sim[v] = sim(p(v), v) (device
  * float [N], 0 for a root): the cosine of each state with its predecessor, from the same
- * products (the graph reward's endpoint similarity). */
+ * products (the graph reward's endpoint similarity).  A prompt's labels (relative to its first
+ * state) and similarities are the same bits wherever it stands in a batch, and alone. */
 ga_status graphattn_forest_classes(ga_forest* forest, const void* embeddings, int32_t dim,
                                    int32_t dtype, float kappa, int32_t* labels, float* edge_sim,
                                    void* hip_stream);

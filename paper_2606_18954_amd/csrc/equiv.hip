@@ -153,12 +153,17 @@ __global__ __launch_bounds__(512, 4) void k_prompt_classes(EquivArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, kg = lane >> 4;
   const int nt = (n + 15) >> 4;                   // 16-row tiles holding states
+  unsigned mix = *reinterpret_cast<const unsigned*>(a.z + (int64_t)(s0 + min(lane, n - 1)) * a.dim) *
+                 (2 * lane + 1);
   if (tid < kPromptMax) {
     s_rep[tid] = tid;
     s_tin[tid] = tid < n ? a.tin[s0 + tid] : 0;
     s_tout[tid] = tid < n ? a.tout[s0 + tid] : 0;
     s_par[tid] = tid < n ? a.parent[s0 + tid] - s0 : -1;   // prompt-local (< 0 for the root)
   }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) mix += __shfl_xor((int)mix, o);
+  mix *= 2654435761u;
   __syncthreads();
 
   // Copies: wave w issues instructions q = 2w and 2w + 1 of every stage; instruction q fills rows
@@ -177,8 +182,10 @@ __global__ __launch_bounds__(512, 4) void k_prompt_classes(EquivArgs a) {
   const int nst = a.dim / kPKC;
   // Workgroups start at different components and wrap around: rows of a power-of-two width lie on
   // one memory channel at a time, and all prompts at the same stage crowd onto few of them (182 us
-  // with one start for all, 165 with 64).
-  const int st0 = (int)((int64_t)((blockIdx.x >> 3) & 63) * nst >> 6);
+  // with one start for all, 165 with 64).  The start follows from the prompt's own embeddings (the
+  // first two components of its first 64 states), not from its place in the batch, so a prompt's
+  // sums are taken in the same order, and have the same bits, wherever it stands.
+  const int st0 = (int)((int64_t)(__builtin_amdgcn_readfirstlane((int)mix) >> 26 & 63) * nst >> 6);
   auto issue = [&](int st) {
     const int at = st0 + st < nst ? st0 + st : st0 + st - nst;
 #pragma unroll

@@ -223,3 +223,43 @@ def test_classes_and_similarities_at_tile_edges(sizes, dim):
         say(f"[equiv] similarity max|d| = {err:.1e}")
         assert err <= 2 * (dim + 8) * 2.0 ** -24
         assert np.array_equal(f.classes(z.cuda(), kappa).cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("n,dim", [(1, 64), (40, 512), (205, 4096), (256, 2048), (300, 1024)])
+def test_a_prompt_has_the_same_bits_anywhere(n, dim):
+    """One prompt alone, and at seventeen places among other prompts: the same bits of its
+    similarities and the same classes (also for a threshold at one of its own cosines, where the
+    last bit decides)."""
+    require_gpu()
+    rng = np.random.default_rng(n)
+    fill = 12
+    one, other = ragged_forest([n], n), ragged_forest([fill], 3)
+    zo = W.draw_state_embeddings(one, dim, n, share=2.0)
+    parts, zs, at = [], [], []
+    pos = 0
+    for k in range(17):
+        parts.append(np.where(one < 0, -1, one + pos))
+        zs.append(zo)
+        at.append(pos)
+        pos += n
+        for _ in range(int(rng.integers(1, 12))):
+            parts.append(np.where(other < 0, -1, other + pos))
+            zs.append(torch.randn((fill, dim), generator=torch.Generator().manual_seed(pos)).bfloat16())
+            pos += fill
+    z, parent = torch.cat(zs).cuda(), np.concatenate(parts).astype(np.int32)
+
+    def classes(par, emb, kappa):
+        with G.Forest(par) as f:
+            es = torch.full((len(par),), -7.0, dtype=torch.float32, device="cuda")
+            lab = f.classes(emb, kappa, edge_sim=es)
+            torch.cuda.synchronize()
+            return lab.cpu().numpy(), es.cpu().numpy()
+
+    lab1, es1 = classes(one, zo.cuda(), 0.75)
+    for kappa in {0.75, float(np.sort(es1)[n // 2])}:
+        lab1, es1 = classes(one, zo.cuda(), kappa)
+        lab, es = classes(parent, z, kappa)
+        for a in at:
+            assert np.array_equal(es[a:a + n].view(np.int32), es1.view(np.int32)), (kappa, a)
+            assert np.array_equal(lab[a:a + n] - a, lab1), (kappa, a)
+    say(f"[case] {n} x {dim}: {len(at)} places, {len(parent)} states")
