@@ -16,6 +16,7 @@
 // deeper than u (shared edges only point deeper, so the graph stays acyclic).  One thread per
 // state counts them over its prompt's states, and a second pass writes the CSR offsets and the
 // lists in ascending state order.
+#include "equiv_tiles.hpp"
 #include "ga_internal.hpp"
 
 #include <type_traits>
@@ -342,9 +343,9 @@ __global__ __launch_bounds__(512, 4) void k_prompt_classes(EquivArgs a) {
 // tile's rows and columns are the diagonals of four more products per wave (two row strips and two
 // column strips each: every wave orders its strips so that those come first), so no pass over the
 // embeddings is needed for them.  A quadrant without states, or below the diagonal, only takes part
-// in the copies and norms.  The host deals the tiles of one prompt to one XCD, whose L2 then
-// serves all but the first read of a row.
-constexpr int kTile = 128;
+// in the copies and norms.  The host deals the tiles of a prompt to as few XCDs as the balance
+// allows, whose L2s then serve all but the first read of a row.
+constexpr int kTile = kEquivTile;
 constexpr int kTStage = 2 * kTile * kPRow;        // rows, then columns: 16 KiB
 constexpr int kTRing = 3;
 

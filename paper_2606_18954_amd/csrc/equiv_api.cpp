@@ -11,6 +11,7 @@
 #include <string>
 #include <vector>
 
+#include "equiv_tiles.hpp"
 #include "ga_internal.hpp"
 
 namespace ga {
@@ -52,39 +53,6 @@ struct Forest {
 };
 
 constexpr int32_t kPromptMax = 256;   // states one workgroup classifies on its own
-
-// The upper-triangle tiles of the prompts [first, end).  Workgroups go to the 8 XCDs in turn, so
-// entry 8 k + x runs on XCD x: with 8 prompts and more, all tiles of a prompt are dealt to one XCD
-// (the one with the least work so far), whose L2 then holds what they share; fewer prompts are
-// spread, or XCDs would idle.  Narrow tiles (at most 64 columns), which take about a third of the
-// time, go last and fill the gaps.  Lists are padded with empty tiles.
-std::vector<int4> tile_list(const std::vector<int2>& prompts) {
-  constexpr int32_t kTile = 128;
-  constexpr int kXcds = 8;
-  const int lists = prompts.size() >= (size_t)kXcds ? kXcds : 1;
-  std::vector<int4> full[kXcds], narrow[kXcds];
-  int64_t load[kXcds] = {0};
-  for (const int2& p : prompts) {
-    const int x = (int)(std::min_element(load, load + lists) - load);
-    for (int32_t i0 = p.x; i0 < p.y; i0 += kTile)
-      for (int32_t j0 = i0; j0 < p.y; j0 += kTile) {
-        const bool wide = p.y - j0 > kTile / 2;
-        (wide ? full : narrow)[x].push_back(make_int4(i0, j0, p.y, 0));
-        load[x] += wide ? 3 : 1;
-      }
-  }
-  size_t longest = 0;
-  for (int x = 0; x < lists; ++x) {
-    full[x].insert(full[x].end(), narrow[x].begin(), narrow[x].end());
-    longest = std::max(longest, full[x].size());
-  }
-  std::vector<int4> out;
-  out.reserve(longest * lists);
-  for (size_t k = 0; k < longest; ++k)
-    for (int x = 0; x < lists; ++x)
-      out.push_back(k < full[x].size() ? full[x][k] : make_int4(0, 0, 0, 0));
-  return out;
-}
 
 // Each prompt's states are consecutive, its root first; p(v) < v.  Depths, prompt ranges and
 // Euler intervals (tin <= tin' < tout exactly when the state is an ancestor of the other).
@@ -165,7 +133,7 @@ ga_status build_forest(const ga_state_forest* f, bool with_items, Forest* fo) {
       for (int32_t v = r; v < e; ++v) fo->big.push_back(v);
       large.push_back(make_int2(r, e));
     }
-    fo->items = tile_list(large);
+    fo->items = ga::equiv_tiles(large);
   }
   return GA_OK;
 }
