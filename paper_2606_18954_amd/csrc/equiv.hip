@@ -87,8 +87,9 @@ __device__ __forceinline__ void dma16(unsigned off, const void* base, unsigned l
 }
 #pragma clang diagnostic pop
 
-// s_waitcnt vmcnt(n) for a runtime n in [0, 15] (expcnt and lgkmcnt left alone).
-#define EQ_VMCNT(k) (((k) & 15) | (7 << 4) | (15 << 8))
+// s_waitcnt vmcnt(n) for a runtime n in [0, 4] (expcnt and lgkmcnt left alone; the encoding splits
+// vmcnt into bits [3:0] and [15:14]).
+#define EQ_VMCNT(k) (((k) & 15) | (7 << 4) | (15 << 8) | (((k) >> 4) << 14))
 __device__ __forceinline__ void wait_vm(int n) {
   asm volatile("" ::: "memory");
   switch (n) {
@@ -97,6 +98,20 @@ __device__ __forceinline__ void wait_vm(int n) {
     case 2: __builtin_amdgcn_s_waitcnt(EQ_VMCNT(2)); break;
     case 3: __builtin_amdgcn_s_waitcnt(EQ_VMCNT(3)); break;
     default: __builtin_amdgcn_s_waitcnt(EQ_VMCNT(4)); break;
+  }
+}
+
+// The same for n copies of each of AHEAD pieces, n in [0, 4].
+template <int AHEAD>
+__device__ __forceinline__ void wait_stages(int n) {
+  static_assert(4 * AHEAD < 64, "vmcnt counts to 63");
+  asm volatile("" ::: "memory");
+  switch (n) {
+    case 0: break;                                // (no copies at all)
+    case 1: __builtin_amdgcn_s_waitcnt(EQ_VMCNT(AHEAD)); break;
+    case 2: __builtin_amdgcn_s_waitcnt(EQ_VMCNT(2 * AHEAD)); break;
+    case 3: __builtin_amdgcn_s_waitcnt(EQ_VMCNT(3 * AHEAD)); break;
+    default: __builtin_amdgcn_s_waitcnt(EQ_VMCNT(4 * AHEAD)); break;
   }
 }
 
@@ -332,22 +347,37 @@ __global__ __launch_bounds__(512, 4) void k_prompt_classes(EquivArgs a) {
   }
 }
 
-// Prompts of more than 256 states: 128 x 128 tiles of their upper triangles, one workgroup each.
+// Prompts of more than 256 states: tiles of their upper triangles, one workgroup each; 128 x 128, or
+// 64 x 64 in batches of few tiles (the host's choice, equiv_tiles.hpp).
 //
-// What bounds it: the L2 reads and LDS reads of the operands against the matrix cores.  64 x 64
-// tiles (16 flops per operand byte) staged through registers, after a pass of their own over the
-// embeddings for the norms, took 322 + 42 us for 64 prompts of 517 states and width 4096; this
-// kernel takes 165 us (590 TFLOP/s over its whole tiles) and no pass before it.
-// Four waves hold a 64 x 64 quadrant each (16 tiles from 8 operand reads per stage); the stages'
-// ring (3 x 16 KiB, two in flight) lets three workgroups share a CU.  The squared norms of a
-// tile's rows and columns are the diagonals of four more products per wave (two row strips and two
-// column strips each: every wave orders its strips so that those come first), so no pass over the
-// embeddings is needed for them.  A quadrant without states, or below the diagonal, only takes part
-// in the copies and norms.  The host deals the tiles of a prompt to as few XCDs as the balance
-// allows, whose L2s then serve all but the first read of a row.
-constexpr int kTile = kEquivTile;
-constexpr int kTStage = 2 * kTile * kPRow;        // rows, then columns: 16 KiB
-constexpr int kTRing = 3;
+// What bounds it: with many tiles, the L2 reads and LDS reads of the operands against the matrix
+// cores.  64 x 64 tiles (16 flops per operand byte) staged through registers, after a pass of their own
+// over the embeddings for the norms, took 322 + 42 us for 64 prompts of 517 states and width 4096; 128
+// x 128 tiles take 165 us (590 TFLOP/s over whole tiles) and no pass before them.  With few, the chain
+// of stages of one tile, each a barrier, the operand reads and the products one after another (about
+// 1,200 cycles at 128 x 128 and 32 components): smaller tiles in stages of 64 components shorten it.
+// One prompt of 300 states, us a call: 128 x 128 64, the register-staged tiles 37, 64 x 64 in stages of
+// 32 components (ring of four) 37, in stages of 64 26; 8 of 517 67, 60, 43 and 35.  (More stages in
+// flight change nothing: a ring of nine 128 x 128 stages 66.)
+// Four waves hold a quadrant each (64 x 64: 16 tiles of 16 x 16 from 8 operand reads per 32
+// components; 32 x 32: 4 from 4).  The ring (3 stages of 16 KiB with two in flight, or 2 with one)
+// lets three or four workgroups share a CU.  The squared norms of a tile's rows and columns are the
+// diagonals of more products per wave (a half of its quadrant's row strips and of its column strips:
+// every wave orders its strips so that those come first), so no pass over the embeddings is needed
+// for them.  A quadrant without states, or below the diagonal, only takes part in the copies and
+// norms.  Both sizes sum in the same order, so a prompt's bits do not depend on the batch.  The host
+// deals the tiles of a prompt to as few XCDs as the balance allows, whose L2s then serve all but the
+// first read of a row.
+template <int Q>                                  // 16-state strips along a quadrant: 4 or 2
+struct TCfg {
+  static constexpr int TILE = 32 * Q;
+  static constexpr int KS = Q == 4 ? 1 : 2;       // pieces of 32 components of a stage
+  static constexpr int HALF = TILE * kPRow;       // rows (then columns) of a piece
+  static constexpr int PIECE = 2 * HALF;
+  static constexpr int STAGE = KS * PIECE;        // 16 KiB
+  static constexpr int RING = Q == 4 ? 3 : 2;
+  static constexpr int WPC = Q == 4 ? 3 : 4;      // workgroups per CU
+};
 
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
@@ -363,9 +393,13 @@ __global__ void k_rep_init(EquivArgs a) {
   if (i < a.n_big) a.rep[a.big[i]] = a.big[i];
 }
 
-__global__ __launch_bounds__(256, 3) void k_sim_union(EquivArgs a) {
-  __shared__ __align__(1024) unsigned char ring[kTRing * kTStage];
-  __shared__ float s_inv[2][kTile];
+template <int Q>
+__global__ __launch_bounds__(256, TCfg<Q>::WPC) void k_sim_union(EquivArgs a) {
+  using C = TCfg<Q>;
+  constexpr int H = Q / 2;                        // row (and column) strips a wave copies, and sums
+                                                  // the norms of
+  __shared__ __align__(1024) unsigned char ring[C::RING * C::STAGE];
+  __shared__ float s_inv[2][C::TILE];
   const int4 it = a.items[blockIdx.x];            // (first row state, first column state, prompt end)
   const int i0 = it.x, j0 = it.y, pend = it.z;
   if (i0 >= pend) return;                         // (pads an XCD's list)
@@ -374,93 +408,102 @@ __global__ __launch_bounds__(256, 3) void k_sim_union(EquivArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, kg = lane >> 4;
   const int wm = wave >> 1, wn = wave & 1;
-  const int nst = a.dim / kPKC;
-  // Copies: each wave fills row strips 2 w and 2 w + 1 and, off the diagonal, the column strips of
+  const int nst = a.dim / (kPKC * C::KS);         // (the width is a multiple of 64)
+  // Copies: each wave fills row strips H w .. H w + H - 1 and, off the diagonal, the column strips of
   // those numbers; strips without states are left out, rows past the prompt re-read its last state.
-  const unsigned short* src[4];
-  bool have[4];
+  const unsigned short* src[Q];
+  bool have[Q];
   int ncp = 0;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int first = (j < 2 ? i0 : j0) + 16 * (2 * wave + (j & 1));
+  for (int j = 0; j < Q; ++j) {
+    const int first = (j < H ? i0 : j0) + 16 * (H * wave + j % H);
     const int row = min(first + (lane >> 2), pend - 1);
     const int chunk = (lane & 3) ^ ((lane >> 3) & 3);
     src[j] = a.z + (int64_t)row * a.dim + chunk * 8;
-    have[j] = first < pend && (j < 2 || !diag);
+    have[j] = first < pend && (j < H || !diag);
     ncp += have[j];
   }
   const unsigned lds_ring = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)ring;
   auto issue = [&](unsigned slot) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < Q; ++j)
       if (have[j]) {
-        dma16_at(src[j], __builtin_amdgcn_readfirstlane(lds_ring + slot + (j >> 1) * (kTStage / 2) +
-                                                        (2 * wave + (j & 1)) * 1024));
-        src[j] += kPKC;
+#pragma unroll
+        for (int k = 0; k < C::KS; ++k) {
+          dma16_at(src[j], __builtin_amdgcn_readfirstlane(lds_ring + slot + k * C::PIECE +
+                                                          (j / H) * C::HALF +
+                                                          (H * wave + j % H) * 1024));
+          src[j] += kPKC;
+        }
       }
   };
-  // Strip x of the wave's rows and of its columns: the two whose norms it computes come first.
-  auto rstrip = [&](int x) { return 4 * wm + (x ^ (2 * wn)); };
-  auto cstrip = [&](int y) { return 4 * wn + (y ^ (2 * wm)); };
-  const int fo = poff(r16, kg), cbase = diag ? 0 : kTStage / 2;
-  f32x4 acc[4][4], sa[2], sb[2];
+  // Strip x of the wave's rows and of its columns: those whose norms it computes come first.
+  auto rstrip = [&](int x) { return Q * wm + (x ^ (H * wn)); };
+  auto cstrip = [&](int y) { return Q * wn + (y ^ (H * wm)); };
+  const int fo = poff(r16, kg), cbase = diag ? 0 : C::HALF;
+  f32x4 acc[Q][Q], sa[H], sb[H];
 #pragma unroll
-  for (int x = 0; x < 2; ++x) sa[x] = sb[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int x = 0; x < H; ++x) sa[x] = sb[x] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int x = 0; x < 4; ++x) {
+  for (int x = 0; x < Q; ++x) {
 #pragma unroll
-    for (int y = 0; y < 4; ++y) acc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int y = 0; y < Q; ++y) acc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
   auto stages = [&](auto quad) {
-    constexpr int NS = decltype(quad)::value ? 4 : 2;
-    unsigned slot = 0, fill = 2 * kTStage;
+    constexpr int NS = decltype(quad)::value ? Q : H;
+    unsigned slot = 0, fill = (C::RING - 1) * C::STAGE;
     // The norms' sums are all of one sign and lose most where a chain of products is long (3.9e-7
-    // against 3.1e-7 of the similarities at width 4096), so they are taken over 4 stages at a time.
-    for (int b0 = 0; b0 < nst; b0 += 4) {
-      const int b1 = min(b0 + 4, nst);
-      f32x4 qa[2], qb[2];
+    // against 3.1e-7 of the similarities at width 4096), so they are taken over 128 components at
+    // a time.
+    for (int b0 = 0; b0 < nst; b0 += 4 / C::KS) {
+      const int b1 = min(b0 + 4 / C::KS, nst);
+      f32x4 qa[H], qb[H];
 #pragma unroll
-      for (int x = 0; x < 2; ++x) qa[x] = qb[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int x = 0; x < H; ++x) qa[x] = qb[x] = f32x4{0.f, 0.f, 0.f, 0.f};
       for (int st = b0; st < b1; ++st) {
-        wait_vm(st + 1 < nst ? ncp : 0);          // this wave's copies of the stage have landed
+        // This wave's copies of the stage have landed ...
+        if (st + C::RING - 2 < nst) wait_stages<C::KS * (C::RING - 2)>(ncp);
+        else wait_vm(0);
         ring_barrier();                           // ... and every wave's; the stage before is done
-        if (st + 2 < nst) issue(fill);
-        bf16x8 av[NS], bv[NS];
+        if (st + C::RING - 1 < nst) issue(fill);
 #pragma unroll
-        for (int x = 0; x < NS; ++x) {
-          av[x] = *reinterpret_cast<const bf16x8*>(ring + slot + rstrip(x) * 1024 + fo);
-          bv[x] = *reinterpret_cast<const bf16x8*>(ring + slot + cbase + cstrip(x) * 1024 + fo);
-        }
+        for (int k = 0; k < C::KS; ++k) {
+          bf16x8 av[NS], bv[NS];
 #pragma unroll
-        for (int x = 0; x < 2; ++x) {
-          qa[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[x], av[x], qa[x], 0, 0, 0);
-          qb[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv[x], bv[x], qb[x], 0, 0, 0);
-        }
-        if constexpr (NS == 4) {
+          for (int x = 0; x < NS; ++x) {
+            av[x] = *reinterpret_cast<const bf16x8*>(ring + slot + k * C::PIECE + rstrip(x) * 1024 + fo);
+            bv[x] = *reinterpret_cast<const bf16x8*>(ring + slot + k * C::PIECE + cbase + cstrip(x) * 1024 + fo);
+          }
 #pragma unroll
-          for (int x = 0; x < 4; ++x)
+          for (int x = 0; x < H; ++x) {
+            qa[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[x], av[x], qa[x], 0, 0, 0);
+            qb[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv[x], bv[x], qb[x], 0, 0, 0);
+          }
+          if constexpr (NS == Q) {
 #pragma unroll
-            for (int y = 0; y < 4; ++y)
-              acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[x], bv[y], acc[x][y], 0, 0, 0);
+            for (int x = 0; x < Q; ++x)
+#pragma unroll
+              for (int y = 0; y < Q; ++y)
+                acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[x], bv[y], acc[x][y], 0, 0, 0);
+          }
         }
         fill = slot;
-        slot = slot + kTStage == kTRing * kTStage ? 0 : slot + kTStage;
+        slot = slot + C::STAGE == C::RING * C::STAGE ? 0 : slot + C::STAGE;
       }
 #pragma unroll
-      for (int x = 0; x < 2; ++x) {
+      for (int x = 0; x < H; ++x) {
         sa[x] += qa[x];
         sb[x] += qb[x];
       }
     }
   };
-  issue(0);
-  if (nst > 1) issue(kTStage);
-  const bool quad = i0 + 64 * wm < pend && j0 + 64 * wn < pend && !(diag && wm > wn);
+  for (int st = 0; st < C::RING - 1 && st < nst; ++st) issue(st * C::STAGE);
+  const bool quad = i0 + 16 * Q * wm < pend && j0 + 16 * Q * wn < pend && !(diag && wm > wn);
   if (quad) stages(std::true_type{});
   else stages(std::false_type{});
   // Squared norms: row m of a strip sits in lane (r16 = m, kg = m / 4), element m % 4.
 #pragma unroll
-  for (int x = 0; x < 2; ++x)
+  for (int x = 0; x < H; ++x)
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       if (4 * kg + i == r16) {
@@ -474,13 +517,13 @@ __global__ __launch_bounds__(256, 3) void k_sim_union(EquivArgs a) {
   // strip y): a bit (16 x + 4 y + i) per cosine that reaches kappa, then the links.
   uint64_t hits = 0;
 #pragma unroll
-  for (int y = 0; y < 4; ++y) {
+  for (int y = 0; y < Q; ++y) {
     const int v = j0 + 16 * cstrip(y) + r16;
     if (v >= pend) continue;
     const float nv = s_inv[1][v - j0];
     const int pv = a.edge_sim ? a.parent[v] : -1;
 #pragma unroll
-    for (int x = 0; x < 4; ++x)
+    for (int x = 0; x < Q; ++x)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int u = i0 + 16 * rstrip(x) + 4 * kg + i;
@@ -656,8 +699,10 @@ hipError_t launch_equivalence(const EquivArgs& a, hipStream_t stream) {
     hipLaunchKernelGGL(k_prompt_classes, dim3((unsigned)a.n_prompts), dim3(512), 0, stream, a);
   if (a.n_big > 0) {
     hipLaunchKernelGGL(k_rep_init, dim3((unsigned)((a.n_big + 255) / 256)), dim3(256), 0, stream, a);
-    if (a.n_items > 0)
-      hipLaunchKernelGGL(k_sim_union, dim3((unsigned)a.n_items), dim3(256), 0, stream, a);
+    if (a.n_items > 0 && a.tile == TCfg<4>::TILE)
+      hipLaunchKernelGGL(k_sim_union<4>, dim3((unsigned)a.n_items), dim3(256), 0, stream, a);
+    else if (a.n_items > 0)
+      hipLaunchKernelGGL(k_sim_union<2>, dim3((unsigned)a.n_items), dim3(256), 0, stream, a);
     hipLaunchKernelGGL(k_labels, dim3((unsigned)((a.n_big + 255) / 256)), dim3(256), 0, stream, a);
   }
   return hipGetLastError();

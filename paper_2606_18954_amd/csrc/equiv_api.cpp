@@ -44,7 +44,7 @@ size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 struct Forest {
   int64_t N = 0;
   std::vector<int32_t> parent, depth, tin, tout, pstart, pend;
-  std::vector<int4> items;       // 128 x 128 tiles of the prompts of more than 256 states
+  ga::EquivTiles tiles;          // of the prompts of more than 256 states
   std::vector<int2> prompts;     // (first state, states) of the prompts of at most 256 states
   std::vector<int32_t> big;      // the states of the larger prompts
   std::vector<int2> all;         // (first state, states) of every prompt
@@ -111,7 +111,7 @@ ga_status build_forest(const ga_state_forest* f, bool with_items, Forest* fo) {
       }
     }
   }
-  fo->items.clear();
+  fo->tiles.items.clear();
   fo->prompts.clear();
   fo->big.clear();
   fo->all.clear();
@@ -133,7 +133,7 @@ ga_status build_forest(const ga_state_forest* f, bool with_items, Forest* fo) {
       for (int32_t v = r; v < e; ++v) fo->big.push_back(v);
       large.push_back(make_int2(r, e));
     }
-    fo->items = ga::equiv_tiles(large);
+    fo->tiles = ga::equiv_tiles(large);
   }
   return GA_OK;
 }
@@ -189,12 +189,12 @@ ga_status forest_create(const ga_state_forest* forest, hipStream_t stream, ga_fo
     return rc;
   }
   const Forest& fo = f->fo;
-  if ((int64_t)fo.items.size() > 0x7fffffffLL) {
+  if ((int64_t)fo.tiles.items.size() > 0x7fffffffLL) {
     delete f;
     return efail(GA_EINVAL, "too many tiles");
   }
   const size_t n4 = align256(4 * fo.N), n8 = align256(8 * fo.N);
-  const size_t up = 6 * n4 + align256(sizeof(int4) * fo.items.size()) +
+  const size_t up = 6 * n4 + align256(sizeof(int4) * fo.tiles.items.size()) +
                     align256(sizeof(int2) * fo.prompts.size()) + align256(4 * fo.big.size()) +
                     align256(sizeof(int2) * fo.all.size());
   const size_t nblk = (size_t)((fo.N + 255) / 256);
@@ -222,7 +222,7 @@ ga_status forest_create(const ga_state_forest* forest, hipStream_t stream, ga_fo
   put(pin, o, fo.depth);
   put(pin, o, fo.pstart);
   put(pin, o, fo.pend);
-  put(pin, o, fo.items);
+  put(pin, o, fo.tiles.items);
   put(pin, o, fo.prompts);
   put(pin, o, fo.big);
   put(pin, o, fo.all);
@@ -234,7 +234,7 @@ ga_status forest_create(const ga_state_forest* forest, hipStream_t stream, ga_fo
   f->pstart = reinterpret_cast<int32_t*>(d + 4 * n4);
   f->pend = reinterpret_cast<int32_t*>(d + 5 * n4);
   f->items = reinterpret_cast<int4*>(d + 6 * n4);
-  const size_t oi = 6 * n4 + align256(sizeof(int4) * fo.items.size());
+  const size_t oi = 6 * n4 + align256(sizeof(int4) * fo.tiles.items.size());
   f->prompts = reinterpret_cast<int2*>(d + oi);
   f->big = reinterpret_cast<int32_t*>(d + oi + align256(sizeof(int2) * fo.prompts.size()));
   f->all = reinterpret_cast<int2*>(d + oi + align256(sizeof(int2) * fo.prompts.size()) +
@@ -285,11 +285,12 @@ ga_status forest_classes(ga_forest* f, const void* embeddings, int32_t dim, int3
   a.prompts = f->prompts;
   a.big = f->big;
   a.n_prompts = (int64_t)f->fo.prompts.size();
+  a.tile = f->fo.tiles.tile;
   a.n_big = (int64_t)f->fo.big.size();
   a.rep = f->rep;
   a.labels = labels;
   a.N = f->fo.N;
-  a.n_items = (int64_t)f->fo.items.size();
+  a.n_items = (int64_t)f->fo.tiles.items.size();
   a.dim = dim;
   a.kappa = kappa;
   EQ_HIP(ga::launch_equivalence(a, stream), "equivalence launch");

@@ -143,7 +143,7 @@ struct KvWriteArgs {
 };
 
 // Equivalence detection (equiv.hip).  z [N][dim] bf16 bits; items: (first row state, first
-// column state, end of their prompt's states, unused) per 128 x 128 tile, row tile <= column tile.
+// column state, end of their prompt's states, unused) per tile, row tile <= column tile.
 struct EquivArgs {
   const unsigned short* z;
   int* rep;                // [N]  union-find parents
@@ -156,6 +156,7 @@ struct EquivArgs {
   const int32_t* parent;   // [N]
   float* edge_sim;         // [N]  optional output: sim(p(v), v), 0 for a root
   int64_t N, n_items, n_prompts, n_big;
+  int32_t tile;            // states along a tile's side
   int32_t dim;
   float kappa;
 };

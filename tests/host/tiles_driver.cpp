@@ -1,5 +1,5 @@
-// Prints the similarity kernel's work list for prompts of the given sizes: one "first-row
-// first-column end" line per entry.
+// Prints the similarity kernel's tile side and work list for prompts of the given sizes: one
+// "first-row first-column end" line per entry.
 #include "equiv_tiles.hpp"
 
 #include <cstdio>
@@ -13,6 +13,8 @@ int main(int argc, char** argv) {
     prompts.push_back(make_int2(at, at + n));
     at += n;
   }
-  for (const int4& t : ga::equiv_tiles(prompts)) std::printf("%d %d %d\n", t.x, t.y, t.z);
+  const ga::EquivTiles tiles = ga::equiv_tiles(prompts);
+  std::printf("%d\n", tiles.tile);
+  for (const int4& t : tiles.items) std::printf("%d %d %d\n", t.x, t.y, t.z);
   return 0;
 }

@@ -8,7 +8,7 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2606_18954_amd", "csrc")
 HIPCC = "/opt/rocm/bin/hipcc"
-TILE, XCDS = 128, 8
+XCDS, RESIDENT = 8, 4 * 256
 
 
 @pytest.fixture(scope="module")
@@ -25,20 +25,23 @@ def driver(tmp_path_factory):
 
 @pytest.mark.parametrize("sizes", [[], [257], [321, 320], [517] * 64, [517] * 65, [4000] + [300] * 7,
                                    [300] * 7 + [4000], [1500] + [500] * 7, [2000] * 9, [300] * 100,
-                                   list(range(260, 1260, 50)), [257] * 90, [20000, 257]])
+                                   list(range(260, 1260, 50)), [257] * 68, [257] * 69, [20000, 257]])
 def test_tiles_cover_and_balance(driver, sizes):
     r = subprocess.run([driver, *map(str, sizes)], capture_output=True, text=True)
     assert r.returncode == 0
-    tiles = [tuple(map(int, l.split())) for l in r.stdout.splitlines()]
+    side, *lines = r.stdout.splitlines()
+    side, tiles = int(side), [tuple(map(int, l.split())) for l in lines]
+    small = sum((n + 63) // 64 * ((n + 63) // 64 + 1) // 2 for n in sizes)
+    assert side == (64 if small <= RESIDENT else 128)     # small tiles while all run at once
     assert len(tiles) % XCDS == 0
     want, at = [], 0
     for n in sizes:
-        want += [(at + i, at + j, at + n) for i in range(0, n, TILE) for j in range(i, n, TILE)]
+        want += [(at + i, at + j, at + n) for i in range(0, n, side) for j in range(i, n, side)]
         at += n
     assert sorted(t for t in tiles if t[2] > 0) == sorted(want)
     # a tile of at most half the columns counts a third; at most a sixteenth, or one tile, beyond
     # an eighth
-    load = [sum(3 if t[2] - t[1] > TILE // 2 else 1 for t in tiles[x::XCDS] if t[2] > 0)
+    load = [sum(3 if t[2] - t[1] > side // 2 else 1 for t in tiles[x::XCDS] if t[2] > 0)
             for x in range(XCDS)]
     mean = sum(load) / XCDS
     assert max(load) <= max(mean + 3, mean * 17 / 16)

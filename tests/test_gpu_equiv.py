@@ -191,13 +191,17 @@ def ragged_forest(sizes, seed):
 
 SIZES = [([1, 2, 15, 16, 17, 33], 64), ([63, 64, 65], 128), ([127, 128, 129], 64),
          ([191, 192, 193, 205], 192), ([255, 256], 64), ([257, 130], 64), ([320, 321], 128),
-         ([383, 385], 64), ([517], 192), ([641], 64), ([257, 300, 5] * 5, 64)]
+         ([383, 385], 64), ([517], 192), ([641], 64), ([257, 300, 5] * 5, 64),
+         # 64 x 64 tiles (in stages of 64 components) as long as at most 1,024 of them make the
+         # batch, with one stage, an odd number and many; 128 x 128 beyond (1,035 and 1,350 here)
+         ([449, 300], 64), ([300, 257], 256), ([385], 576), ([257] * 68, 64), ([257] * 69, 64),
+         ([257] * 90, 128), ([385] * 50, 192), ([517] * 23, 64)]
 
 
 @pytest.mark.parametrize("sizes,dim", SIZES)
 def test_classes_and_similarities_at_tile_edges(sizes, dim):
     """Prompts at the edges of the 16-state strips, of the 64-state blocks of one workgroup and of
-    the 128-state tiles (whole tiles, narrow ones, empty quadrants), and enough of the larger ones
+    the 64- and 128-state tiles (whole tiles, narrow ones, empty quadrants), and enough of the larger ones
     that their tiles are dealt to the XCDs.  Labels are exact; edge similarities are two fp32 sums
     of `dim` products and a reciprocal root each: within (dim + 8) 2^-24 of the float64 cosine,
     times two for the two norms."""
