@@ -436,8 +436,10 @@ Layout layout(const Sizes& z, const ga_params& p) {
   sz[L_BLK_SUM] = sizeof(int64_t) * ((z.E + 1023) / 1024 + 1);
   // Partials: fp16 values + (lambda, scale) for bf16 inputs, fp32 values + lambda for fp32.
   const bool f16_parts = p.dtype == GA_BF16;
-  sz[L_PO] = (f16_parts ? 2 : 4) * (size_t)z.prows * p.num_q_heads * p.head_dim;
-  sz[L_PLSE] = (f16_parts ? 8 : 4) * (size_t)z.prows * p.num_q_heads;
+  // (none where the attention kernel writes the rows itself)
+  const size_t parts = z.direct ? 0 : (size_t)z.prows * p.num_q_heads;
+  sz[L_PO] = (f16_parts ? 2 : 4) * parts * p.head_dim;
+  sz[L_PLSE] = (f16_parts ? 8 : 4) * parts;
   Layout L{};
   size_t o = 0;
   for (int i = 0; i < L_COUNT; ++i) {

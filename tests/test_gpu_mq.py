@@ -108,6 +108,25 @@ def test_shared_prefix_and_ragged_chains():
         _run(lens, paths, counts, Hq, Hkv, D, 81, True)
 
 
+@pytest.mark.gpu
+def test_rows_written_directly_need_no_partial_buffers():
+    """A plan whose rows the kernel writes itself allocates no partial rows (here 4000 x 28 x 264
+    bytes, 28 MiB); with float32 output, which is merged, it does."""
+    require_gpu()
+    lens = [250] * 16
+    g = W.assemble_graph(lens, [[i] for i in range(16)], 3, 0)
+    torch.cuda.synchronize()
+    took = {}
+    for out_f32 in (False, True):
+        p = G.make_params(28, 4, 128, g.num_pages, "bf16", 0.0, out_f32)
+        free = torch.cuda.mem_get_info()[0]
+        with G.Plan(G.HostGraph.from_graph(g), p, query_counts=lens) as pl:
+            assert pl.info().num_partial_rows == 4000
+            took[out_f32] = free - torch.cuda.mem_get_info()[0]
+    say(f"[case] bytes of a plan: {took}")
+    assert took[True] - took[False] >= 4000 * 28 * 264 - (4 << 20)
+
+
 def test_generated_code(tmp_path):
     """The copies write M0 by inline assembly, so every M0 write must feed one, and no kernel may
     spill (a spill's loads would wait for the copies in flight)."""
