@@ -101,13 +101,13 @@ __device__ __forceinline__ void wait_vm(int n) {
   }
 }
 
-// The same for n copies of each of AHEAD pieces, n in [0, 4].
+// The same for n copies of each of AHEAD pieces, n in [0, 4] (0: waits for all).
 template <int AHEAD>
 __device__ __forceinline__ void wait_stages(int n) {
   static_assert(4 * AHEAD < 64, "vmcnt counts to 63");
   asm volatile("" ::: "memory");
   switch (n) {
-    case 0: break;                                // (no copies at all)
+    case 0: __builtin_amdgcn_s_waitcnt(EQ_VMCNT(0)); break;
     case 1: __builtin_amdgcn_s_waitcnt(EQ_VMCNT(AHEAD)); break;
     case 2: __builtin_amdgcn_s_waitcnt(EQ_VMCNT(2 * AHEAD)); break;
     case 3: __builtin_amdgcn_s_waitcnt(EQ_VMCNT(3 * AHEAD)); break;
@@ -462,8 +462,7 @@ __global__ __launch_bounds__(256, TCfg<Q>::WPC) void k_sim_union(EquivArgs a) {
       for (int x = 0; x < H; ++x) qa[x] = qb[x] = f32x4{0.f, 0.f, 0.f, 0.f};
       for (int st = b0; st < b1; ++st) {
         // This wave's copies of the stage have landed ...
-        if (st + C::RING - 2 < nst) wait_stages<C::KS * (C::RING - 2)>(ncp);
-        else wait_vm(0);
+        wait_stages<C::KS * (C::RING - 2)>(st + C::RING - 2 < nst ? ncp : 0);
         ring_barrier();                           // ... and every wave's; the stage before is done
         if (st + C::RING - 1 < nst) issue(fill);
 #pragma unroll
