@@ -40,29 +40,35 @@ HBM_PEAK_GBS = 8000.0
 MFMA_BF16_PEAK_TFLOPS = 2500.0
 METRIC = "branch-tokens/s per decode step; % of HBM roofline on unique KV bytes"
 COUNTERS_MD = os.path.join(ROOT, "profiles", "seg_attn_merged_dag_counters.md")
-EXT_COUNTERS_MD = os.path.join(ROOT, "profiles", "seg_attn_extend_counters.md")
+EXT_COUNTERS_MD = os.path.join(ROOT, "profiles", "mq_attn_extend_counters.md")
 EQ_COUNTERS_MD = os.path.join(ROOT, "profiles", "equiv_classes_counters.md")
-KERNEL_SRC = os.path.join(ROOT, "paper_2606_18954_amd", "csrc", "seg_attn.hip")
-EQ_KERNEL_SRC = os.path.join(ROOT, "paper_2606_18954_amd", "csrc", "equiv.hip")
+CSRC = os.path.join(ROOT, "paper_2606_18954_amd", "csrc")
+# The sources whose change makes a kernel's committed counters stale: its own and its headers.
+KERNEL_SRCS = ("seg_attn.hip", "attn_dev.hpp", "ga_internal.hpp")
+EXT_KERNEL_SRCS = ("mq_attn.hip", "attn_dev.hpp", "ga_internal.hpp")
+EQ_KERNEL_SRCS = ("equiv.hip", "equiv_tiles.hpp", "attn_dev.hpp", "ga_internal.hpp")
 
 
 def log(msg):
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
 
 
-def kernel_hash(src=KERNEL_SRC):
-    with open(src, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+def kernel_hash(srcs=KERNEL_SRCS):
+    h = hashlib.sha256()
+    for name in srcs:
+        with open(os.path.join(CSRC, name), "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()[:16]
 
 
-def measured_counters(config, path=COUNTERS_MD, src=KERNEL_SRC):
+def measured_counters(config, path=COUNTERS_MD, srcs=KERNEL_SRCS):
     """HBM traffic and MFMA busy fraction from the committed rocprofv3 counter summary, only
-    if it was taken on this exact kernel source and workload."""
+    if it was taken on these exact kernel sources and this workload."""
     if not os.path.exists(path):
         return None
     txt = open(path).read()
     kv = dict(re.findall(r"^- (\w+): (\S+)", txt, flags=re.M))
-    if kv.get("kernel_source_sha256_16") != kernel_hash(src) or kv.get("workload") != config:
+    if kv.get("kernel_source_sha256_16") != kernel_hash(srcs) or kv.get("workload") != config:
         return None
     return kv
 
@@ -273,7 +279,7 @@ def run_extend(args, torch, G, W):
     flops, vis = extend_flops(wl)
     achieved = flops / (attn_ms * 1e-3) / 1e12
     ukv = wl.unique_kv_bytes()
-    cnt = measured_counters("extend", EXT_COUNTERS_MD)
+    cnt = measured_counters("extend", EXT_COUNTERS_MD, EXT_KERNEL_SRCS)
     traffic = None
     if cnt:
         traffic = float(cnt["fetch_bytes_per_launch"]) + float(cnt["write_bytes_per_launch"])
@@ -551,7 +557,7 @@ def run_equiv(args, torch, G, W):
     pairs = compared_pairs_count(wl.parent)
     achieved = zbytes / (ms * 1e-3) / 1e9
     merged = int((lab != np.arange(N)).sum())
-    cnt = measured_counters("equiv", EQ_COUNTERS_MD, EQ_KERNEL_SRC)
+    cnt = measured_counters("equiv", EQ_COUNTERS_MD, EQ_KERNEL_SRCS)
     traffic = None
     if cnt:
         traffic = float(cnt["fetch_bytes_per_launch"]) + float(cnt["write_bytes_per_launch"])
