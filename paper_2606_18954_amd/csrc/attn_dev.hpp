@@ -1,5 +1,5 @@
-// Device helpers shared by the attention kernels (seg_attn.hip, mq_attn.hip): direct-to-LDS
-// copies, partial-row stores, explicit waits and barriers.
+// Device helpers shared by the attention kernels (seg_attn.hip, mq_attn.hip) and the similarity kernels
+// (equiv.hip): direct-to-LDS copies, partial-row stores, explicit waits and barriers.
 #pragma once
 
 #include "ga_internal.hpp"

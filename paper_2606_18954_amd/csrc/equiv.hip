@@ -16,6 +16,7 @@
 // deeper than u (shared edges only point deeper, so the graph stays acyclic).  One thread per
 // state counts them over its prompt's states, and a second pass writes the CSR offsets and the
 // lists in ascending state order.
+#include "attn_dev.hpp"
 #include "equiv_tiles.hpp"
 #include "ga_internal.hpp"
 
@@ -77,27 +78,15 @@ constexpr int kPRow = kPKC * 2;                 // bytes of one state row in a s
 constexpr int kPStage = kPromptMax * kPRow;     // 16 KiB
 constexpr int kPRing = 4;
 
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-// LDS[lds_base + 16 * lane] <- global[base + off] (16 bytes per lane).  M0 holds the LDS base;
-// the kernel keeps no other value in M0, and completion is awaited with explicit vmcnt waits.
-__device__ __forceinline__ void dma16(unsigned off, const void* base, unsigned lds_base) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1"
-               :: "v"(off), "s"(base), "s"(lds_base) : "memory", "m0");
-}
-#pragma clang diagnostic pop
-
-// s_waitcnt vmcnt(n) for a runtime n in [0, 4] (expcnt and lgkmcnt left alone; the encoding splits
-// vmcnt into bits [3:0] and [15:14]).
-#define EQ_VMCNT(k) (((k) & 15) | (7 << 4) | (15 << 8) | (((k) >> 4) << 14))
+// s_waitcnt vmcnt(n) for a runtime n in [0, 4].
 __device__ __forceinline__ void wait_vm(int n) {
   asm volatile("" ::: "memory");
   switch (n) {
-    case 0: __builtin_amdgcn_s_waitcnt(EQ_VMCNT(0)); break;
-    case 1: __builtin_amdgcn_s_waitcnt(EQ_VMCNT(1)); break;
-    case 2: __builtin_amdgcn_s_waitcnt(EQ_VMCNT(2)); break;
-    case 3: __builtin_amdgcn_s_waitcnt(EQ_VMCNT(3)); break;
-    default: __builtin_amdgcn_s_waitcnt(EQ_VMCNT(4)); break;
+    case 0: __builtin_amdgcn_s_waitcnt(GA_VMCNT(0)); break;
+    case 1: __builtin_amdgcn_s_waitcnt(GA_VMCNT(1)); break;
+    case 2: __builtin_amdgcn_s_waitcnt(GA_VMCNT(2)); break;
+    case 3: __builtin_amdgcn_s_waitcnt(GA_VMCNT(3)); break;
+    default: __builtin_amdgcn_s_waitcnt(GA_VMCNT(4)); break;
   }
 }
 
@@ -107,29 +96,12 @@ __device__ __forceinline__ void wait_stages(int n) {
   static_assert(4 * AHEAD < 64, "vmcnt counts to 63");
   asm volatile("" ::: "memory");
   switch (n) {
-    case 0: __builtin_amdgcn_s_waitcnt(EQ_VMCNT(0)); break;
-    case 1: __builtin_amdgcn_s_waitcnt(EQ_VMCNT(AHEAD)); break;
-    case 2: __builtin_amdgcn_s_waitcnt(EQ_VMCNT(2 * AHEAD)); break;
-    case 3: __builtin_amdgcn_s_waitcnt(EQ_VMCNT(3 * AHEAD)); break;
-    default: __builtin_amdgcn_s_waitcnt(EQ_VMCNT(4 * AHEAD)); break;
+    case 0: __builtin_amdgcn_s_waitcnt(GA_VMCNT(0)); break;
+    case 1: __builtin_amdgcn_s_waitcnt(GA_VMCNT(AHEAD)); break;
+    case 2: __builtin_amdgcn_s_waitcnt(GA_VMCNT(2 * AHEAD)); break;
+    case 3: __builtin_amdgcn_s_waitcnt(GA_VMCNT(3 * AHEAD)); break;
+    default: __builtin_amdgcn_s_waitcnt(GA_VMCNT(4 * AHEAD)); break;
   }
-}
-
-// (This wave's operand reads of the stage before have returned, so its slot may be refilled.)
-__device__ __forceinline__ void ring_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(0xC07F);             // lgkmcnt(0)
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
-// A wave-uniform pointer held in scalar registers (both halves read from the first lane as
-// unsigned 32-bit values, so the low half is not sign-extended into the high one).
-__device__ __forceinline__ const void* uniform_ptr(const void* p) {
-  const uint64_t v = (uint64_t)(uintptr_t)p;
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
-  return reinterpret_cast<const void*>((uintptr_t)(((uint64_t)hi << 32) | lo));
 }
 
 __device__ __forceinline__ int poff(int row, int chunk) {
@@ -186,7 +158,7 @@ __global__ __launch_bounds__(512, 4) void k_prompt_classes(EquivArgs a) {
   // 16q .. 16q + 15, lane l the LDS chunk l % 4 of row 16q + l / 4 with the global chunk that
   // the permutation puts there.  Rows past the prompt re-read its last state (valid memory;
   // their products are never used).
-  const void* pbase = uniform_ptr(a.z + (int64_t)s0 * a.dim);
+  const void* pbase = (const void*)uniform64((int64_t)(uintptr_t)(a.z + (int64_t)s0 * a.dim));
   unsigned coff[2];
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
@@ -207,14 +179,15 @@ __global__ __launch_bounds__(512, 4) void k_prompt_classes(EquivArgs a) {
 #pragma unroll
     for (int j = 0; j < 2; ++j)
       if (2 * wave + j < nt)                      // (strips without states are not copied)
-        dma16(coff[j] + (unsigned)(at * kPRow), pbase,
-              __builtin_amdgcn_readfirstlane(lds_ring + (st % kPRing) * kPStage +
-                                             (2 * wave + j) * 1024));
+        dma16_cached(coff[j] + (unsigned)(at * kPRow), pbase,
+                     __builtin_amdgcn_readfirstlane(lds_ring + (st % kPRing) * kPStage +
+                                                    (2 * wave + j) * 1024));
   };
   const int ncp = max(0, min(2, nt - 2 * wave));  // copies of this wave per stage
   auto next_stage = [&](int st) {
     wait_vm(ncp * min(nst - 1 - st, kPRing - 2)); // this wave's copies of stage st have landed
-    ring_barrier();                               // ... and every wave's; stage st - 1 is done
+    lds_barrier();                                // ... and every wave's; stage st - 1 is done (its
+                                                  // operand reads have returned)
     if (st + kPRing - 1 < nst) issue(st + kPRing - 1);
   };
   const int fo = poff(r16, kg);                   // this lane's chunk of a 16-row strip
@@ -350,10 +323,12 @@ __global__ __launch_bounds__(512, 4) void k_prompt_classes(EquivArgs a) {
 // Prompts of more than 256 states: tiles of their upper triangles, one workgroup each; 128 x 128, or
 // 64 x 64 in batches of few tiles (the host's choice, equiv_tiles.hpp).
 //
-// What bounds it: with many tiles, the L2 reads and LDS reads of the operands against the matrix
-// cores.  64 x 64 tiles (16 flops per operand byte) staged through registers, after a pass of their own
-// over the embeddings for the norms, took 322 + 42 us for 64 prompts of 517 states and width 4096; 128
-// x 128 tiles take 165 us (590 TFLOP/s over whole tiles) and no pass before them.  With few, the chain
+// What bounds it: with many tiles, no one unit (64 prompts of 517 states, width 4096: matrix cores busy
+// 34% of the time, vector instructions 22%, LDS 15%, and 0.8 to 1.0 GB read past the L2s for 0.27
+// GB of embeddings) but a barrier per 20 products and the second, partly filled round of tiles.  64 x 64
+// tiles (16 flops per operand byte) staged through registers, after a pass of their own over the
+// embeddings for the norms, took 322 + 42 us; 128 x 128 tiles take 165 us (590 TFLOP/s over whole
+// tiles) and no pass before them.  With few, the chain
 // of stages of one tile, each a barrier, the operand reads and the products one after another (about
 // 1,200 cycles at 128 x 128 and 32 components): smaller tiles in stages of 64 components shorten it.
 // One prompt of 300 states, us a call: 128 x 128 64, the register-staged tiles 37, 64 x 64 in stages of
@@ -463,7 +438,7 @@ __global__ __launch_bounds__(256, TCfg<Q>::WPC) void k_sim_union(EquivArgs a) {
       for (int st = b0; st < b1; ++st) {
         // This wave's copies of the stage have landed ...
         wait_stages<C::KS * (C::RING - 2)>(st + C::RING - 2 < nst ? ncp : 0);
-        ring_barrier();                           // ... and every wave's; the stage before is done
+        lds_barrier();                            // ... and every wave's; the stage before is done
         if (st + C::RING - 1 < nst) issue(fill);
 #pragma unroll
         for (int k = 0; k < C::KS; ++k) {

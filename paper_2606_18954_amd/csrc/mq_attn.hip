@@ -3,17 +3,21 @@
 // the descriptors, the partial rows and the merge shared with it.
 //
 // What bounds it.  With many queries per branch a page is read for a hundred rows and more, so the
-// step is bound by instruction issue: the matrix cores and the softmax's vector instructions share
-// each SIMD, and every copy into LDS holds up the wave that issues it.  Per pair of pages and 32
-// rows (head_dim 128) the matrix cores need 16 x 32 cycles and the vector unit about 560 (16
-// exponentials, 91 others); two waves per SIMD that overlap perfectly would take 1,120 cycles for
-// two such steps.  Measured: 1,950 to 1,990 (the same loop without copies 1,660, and alone on
-// data in LDS 1,500), plus 2,100 before and 8,500 after the loop of a unit.  The kernel this one
-// replaces (seg_attn.hip, 16-row tiles, three workgroups per CU) issued 6 vector instructions per
+// matrix cores, the softmax's vector instructions and LDS matter, and no one of them is full.  Counters
+// over the kernel's time, 16-token extend | prefill (workloads below): matrix cores busy 39% | 43%,
+// vector instructions 40% | 41% of the SIMDs' cycles, LDS active 22% | 25% with 0.1% | 3.5% of its
+// cycles lost to conflicts.  Matrix and vector work together would fill 79% to 84% if they never
+// overlapped, and with two waves per SIMD, each a chain of scores, softmax and products, they overlap
+// little.  Per pair of pages and 32 rows (head_dim 128) the matrix cores need 16 x 32 cycles and the
+// vector unit about 560 (16 exponentials, 91 others); two waves per SIMD that overlap perfectly would
+// take 1,120 cycles for two such steps.  Measured: 1,950 to 1,990 (the same loop without copies 1,660,
+// and alone on data in LDS 1,500), plus 2,100 before and 8,500 after the loop of a unit.  The kernel this
+// one replaces (seg_attn.hip, 16-row tiles, three workgroups per CU) issued 6 vector instructions per
 // matrix instruction of half the size; here it is 7 per instruction of twice the size.
-//   16-token extend of the merged-DAG rollout, 1024 branches, 28/4 heads x 128: 1.445 -> 1.32 ms
-//   (0.72 PFLOP/s); prefill of 32 prompts of 1024 to 2048 tokens: 1.58 -> 0.64 ms and no merge
-//   (0.83 PFLOP/s; a plain 8192^3 bf16 matrix product reaches 1.38 on the same card).
+//   16-token extend of the merged-DAG rollout, 1024 branches, 28/4 heads x 128, average of 50 steps,
+//   other kernel | this one on one card: 1.38 | 1.30 ms (0.75 PFLOP/s); on a card with lower clocks 1.43.
+//   Prefill of 32 prompts of 1024 to 2048 tokens: 1.58 | 0.61 ms, average of 40 passes, and no merge
+//   (0.87 PFLOP/s; a plain 8192^3 bf16 matrix product reaches 1.23 on that card).
 //
 // Layout.  Four waves of one 32-row tile each; two pages (32 tokens) per step:
 //   S^T = K Q^T    v_mfma_f32_32x32x16_bf16: a lane owns one row and half of its 32 scores

@@ -15,8 +15,9 @@
 //              at most kSpreadFloor is none: rewards equal by the definition differ by rounding).
 //   efficiency per class of two or more (found by its smallest member): the deepest proper
 //              ancestor a_Q of all members, route lengths l = d(v) - d(a_Q), z-scores of -l
-//              gated by the class's mean defined score; every edge then sums, in ascending
-//              state order, the values of the members in its subtree whose anchor lies above it.
+//              gated by the class's mean defined score; every edge then sums, in a fixed order
+//              (ascending state or Euler order), the values of the members in its subtree whose
+//              anchor lies above it.
 //   dual       A_dual = A_cor + lambda A_eff.
 // Every value is computed in a fixed order, so the results are deterministic.
 #include "ga_internal.hpp"
